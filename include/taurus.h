@@ -418,7 +418,14 @@ void taurus_plan_destroy(taurus_plan* plan);
  * every vertex's pending-message count to |M(v)| + 1 (the self message
  * counts as one arrival).  Without a budget the dense accumulators are
  * allocated first and hold the index build's temporaries until the first
- * push.  *out receives the handle.  Blocks until the index is built.
+ * push.  A sampled in-core layer with device outputs, no profile, fp32 or
+ * bf16 inputs of at most 256 columns whose rows take at most 8 * d_out
+ * bytes, and a sample that leaves out some edge, is aggregated by
+ * destination instead: it keeps the sample as in-edge lists, its pushes copy
+ * x into a table of all rows (allocated by the first push), and
+ * taurus_finalize evaluates every destination whose messages have all been
+ * pushed.  If its first chunk comes from the host it is broadcast like the
+ * others.  *out receives the handle.  Blocks until the index is built.
  * Errors: TAURUS_E_INVALID for bad arguments or a graph that is not a valid
  * simple CSR; TAURUS_E_BUDGET when the budget cannot hold the layer;
  * TAURUS_E_OOM / TAURUS_E_DEVICE from the runtime.  On error *out is NULL.
@@ -448,8 +455,8 @@ int taurus_push_chunk(taurus_layer* L, int64_t src_begin, int64_t src_end, const
 /*
  * Wait for the layer's work, check that every destination completed (Sec.
  * 3.6: a vertex graduates once its pending count reaches zero, its output
- * row written by the flush that completes it) and fill *stats (may be
- * NULL).  Returns TAURUS_E_INCOMPLETE (with the count in
+ * row written by the flush that completes it; a layer aggregated by
+ * destination writes its rows here) and fill *stats (may be NULL).  Returns TAURUS_E_INCOMPLETE (with the count in
  * stats->pending_left) if some destination still has pending messages, e.g.
  * because a chunk was never pushed.  After TAURUS_OK every row of desc.out
  * holds its final value.

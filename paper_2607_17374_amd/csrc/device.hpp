@@ -23,22 +23,25 @@ __device__ inline uint32_t f32_to_f16_bits(float f) {
     return (uint32_t)__builtin_bit_cast(uint16_t, h);
 }
 
+// Four consecutive output values in 16 bits (dtype 1 bf16, 2 fp16), round
+// to nearest even by the conversion instructions (v_cvt_pk_bf16_f32: one for
+// two values, where the integer form takes about seven each).
+__device__ inline uint2 pack_out4(int dtype, float4 z) {
+    if (dtype == 1) {
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+        return make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{z.x, z.y}), b16x2)),
+                          __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{z.z, z.w}), b16x2)));
+    }
+    return make_uint2(f32_to_f16_bits(z.x) | (f32_to_f16_bits(z.y) << 16),
+                      f32_to_f16_bits(z.z) | (f32_to_f16_bits(z.w) << 16));
+}
+
 // Four consecutive output values at element idx of out, stored as dtype
 // (0 fp32, 1 bf16, 2 fp16).
 __device__ inline void store_out4(void* out, int dtype, int64_t idx, float4 z) {
-    if (dtype == 0) {
-        *reinterpret_cast<float4*>(static_cast<float*>(out) + idx) = z;
-    } else {
-        uint2 p;
-        if (dtype == 1) {
-            p.x = f32_to_bf16_bits(z.x) | (f32_to_bf16_bits(z.y) << 16);
-            p.y = f32_to_bf16_bits(z.z) | (f32_to_bf16_bits(z.w) << 16);
-        } else {
-            p.x = f32_to_f16_bits(z.x) | (f32_to_f16_bits(z.y) << 16);
-            p.y = f32_to_f16_bits(z.z) | (f32_to_f16_bits(z.w) << 16);
-        }
-        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + idx) = p;
-    }
+    if (dtype == 0) *reinterpret_cast<float4*>(static_cast<float*>(out) + idx) = z;
+    else *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + idx) = pack_out4(dtype, z);
 }
 
 // SplitMix64 finaliser and increment (Steele, Lea and Flood, OOPSLA 2014).

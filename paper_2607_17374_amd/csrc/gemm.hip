@@ -49,7 +49,7 @@ void gemm_pack_weights_f32(const float* W, int K, int Nc, std::vector<float>& pa
 
 int gemm_packed_blocks_k16(int k) { return (int)ceil_div(k, 32); }
 
-static uint16_t host_f32_to_bf16(float f) {
+uint16_t host_f32_to_bf16(float f) {
     uint32_t u;
     std::memcpy(&u, &f, 4);
     if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // quiet NaN

@@ -218,5 +218,19 @@ void sample_mask(const taurus_graph& g, const Csc& csc, uint64_t seed, int layer
 int64_t sample_items(const Csc& csc, int64_t n, uint64_t seed, int layer, int k, int64_t C, int vbits,
                      Arena& key_arena, Arena& val_arena, SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad,
                      hipStream_t s);
+// The same sample as lists: off[v] .. off[v + 1] of src, sources ascending
+// (both from arena, the temporaries from tmp).  False, with nothing drawn or
+// held, when the sample is all e in-edges.
+struct SampleLists {
+    int64_t* off = nullptr;   // [n + 1]
+    uint32_t* src = nullptr;  // [kept]
+    int64_t kept = 0;
+    int64_t nonzero = 0;      // destinations with at least one
+};
+bool sample_lists(const Csc& csc, int64_t n, int64_t e, uint64_t seed, int layer, int k, Arena& arena, Arena& tmp,
+                  SampleLists& out, int* bad, hipStream_t s);
+// sample_items' output from those lists
+int64_t list_items(const SampleLists& l, int64_t n, int64_t C, int vbits, Arena& key_arena, Arena& val_arena,
+                   SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad, hipStream_t s);
 
 }  // namespace taurus

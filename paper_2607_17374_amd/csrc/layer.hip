@@ -42,6 +42,7 @@
 #include <thread>
 
 #include "device.hpp"
+#include "gather.hpp"
 #include "gemm_device.hpp"
 #include "internal.hpp"
 #include "resident.hpp"
@@ -1407,10 +1408,12 @@ static double ms_since(std::chrono::steady_clock::time_point t0) {
 
 // A sampled layer's index (sample != null) takes its items straight from the
 // fanout sampler; an exact layer's from every CSR edge.
+// (from lists already drawn, when given).
 struct SampleReq {
     const Csc* csc;
     uint64_t seed;
     int layer, k;
+    const SampleLists* lists;
 };
 
 // scratch (optional): where the build's temporaries go
@@ -1478,8 +1481,11 @@ static std::shared_ptr<ChunkIndex> build_index(const taurus_graph& g, int64_t C,
         // the sampler's kept in-edges come destination-major with sources
         // ascending, so a stable sort by the chunk field alone orders them
         // by (chunk, destination, source)
-        items = sample_items(*sample->csc, n, sample->seed, sample->layer, sample->k, C, vbits, tmp, idx->arena, sb,
-                             idx->m, first_chunk, bad, s);
+        if (sample->lists)
+            items = list_items(*sample->lists, n, C, vbits, tmp, idx->arena, sb, idx->m, first_chunk, bad, s);
+        else
+            items = sample_items(*sample->csc, n, sample->seed, sample->layer, sample->k, C, vbits, tmp, idx->arena,
+                                 sb, idx->m, first_chunk, bad, s);
         radix_sort_u64(sb, items, cbits, tmp, s, bad, 8, nullptr, kshift);
     } else {
         sb.keys[0] = tmp.alloc<uint64_t>(e, "index keys");
@@ -1814,6 +1820,15 @@ struct taurus_layer {
     int32_t* comp_ids = nullptr;
     std::vector<int64_t> comp_off;
     int grad_blocks = 0;
+    // sampled layers kept in core (gather_rule): no index, counts or
+    // accumulators; pushes fill the table, finalize aggregates
+    bool gather = false, gathered = false;
+    taurus::SampleLists lists;       // kept in-edges by destination
+    char* table = nullptr;           // [n][d_in] of in_dtype, allocated by the first push
+    int* gather_bad = nullptr;       // sampler flags, read at finalize
+    uint32_t* gather_ord = nullptr;  // the order destinations are taken in
+    unsigned long long* list_counts = nullptr;
+    std::vector<float> w_host, b_host;   // for a layer that turns out to be fed from the host
     void* wpack_any = nullptr;  // packed weights (fp32 or 16-bit fragments)
     void* out_dev = nullptr;    // desc.out as kernels address it
     std::unique_ptr<taurus::Residency> res;  // accumulator pool under a budget (null: dense rows)
@@ -1964,18 +1979,39 @@ static bool same_graph(const taurus_graph& a, const taurus_graph& b) {
     return a.n == b.n && a.e == b.e && a.row_off == b.row_off && a.col_dst == b.col_dst;
 }
 
-static void layer_init(taurus_layer* L) {
-    const auto t_start = std::chrono::steady_clock::now();
-    // the set-up work goes to desc.setup_stream when given (the layer's
-    // stream waits for it at the end), else to the layer's stream
-    hipStream_t s = L->d.setup_stream ? static_cast<hipStream_t>(L->d.setup_stream) : L->s;
-    L->arena.set_stream(s);
+// the plan's in-edge lists (built by its first user), or the layer's own
+static std::shared_ptr<Csc> layer_csc(taurus_layer* L, hipStream_t s, Arena* scratch) {
+    taurus_plan* plan = const_cast<taurus_plan*>(L->d.plan);
+    if (!plan) return build_csc(L->g, s, scratch);
+    std::lock_guard<std::mutex> lock(plan->mu);
+    if (!plan->csc) {
+        plan->csc = build_csc(L->g, s, scratch);
+        plan->ms_build += plan->csc->ms_build;
+    }
+    return plan->csc;
+}
+
+// the layer's stream takes up the layer's memory and work from the set-up
+// stream s
+static void join_setup(taurus_layer* L, hipStream_t s) {
+    if (s == L->s) return;
+    hipEvent_t ready = nullptr;
+    TAURUS_HIP(hipEventCreateWithFlags(&ready, hipEventDisableTiming));
+    const hipError_t rc1 = hipEventRecord(ready, s);
+    const hipError_t rc2 = rc1 == hipSuccess ? hipStreamWaitEvent(L->s, ready, 0) : rc1;
+    (void)hipEventDestroy(ready);  // released once the wait has been satisfied
+    TAURUS_HIP(rc2);
+    L->arena.set_stream(L->s);
+    if (L->res) L->res->arena.set_stream(L->s);
+}
+
+// Set-up of a layer that broadcasts its chunks: chunk index, counts,
+// weights, accumulators.  lists: the kept in-edges of a sampled layer that
+// drew them already.
+static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* lists) {
     const taurus_graph& g = L->g;
     const taurus_layer_desc& d = L->d;
-    const int64_t n = g.n, C = d.chunk;
-    L->n = n;
-    L->C = C;
-    L->nchunks = ceil_div(n, C);
+    const int64_t n = L->n, C = L->C;
     // accumulator width: the perceptron's hidden width for GIN_MLP
     L->d_o = d.agg == TAURUS_GIN_MLP ? d.d_hidden : d.d_out;
     // GraphSAGE: [W_agg | W_self]; GAT: W and the two attention columns,
@@ -1994,8 +2030,6 @@ static void layer_init(taurus_layer* L) {
     // first user); a sampled layer draws its mask (from the plan's CSC) and
     // builds its own index of the kept edges
     taurus_plan* plan = const_cast<taurus_plan*>(d.plan);
-    if (plan && (!same_graph(plan->g, g) || plan->chunk != C))
-        fail(TAURUS_E_INVALID, "plan was built for another graph or chunk size");
     // Without a budget the accumulators are dense: they are allocated first
     // and, until the first chunk arrives (their rows are logically zero
     // while nothing has arrived and are never cleared), hold the temporaries
@@ -2013,25 +2047,14 @@ static void layer_init(taurus_layer* L) {
     }
     const auto t_index = std::chrono::steady_clock::now();
     if (d.fanout > 0) {
-        std::shared_ptr<Csc> csc;
-        if (plan) {
-            std::lock_guard<std::mutex> lock(plan->mu);
-            if (!plan->csc) {
-                plan->csc = build_csc(g, s, scratch.get());
-                plan->ms_build += plan->csc->ms_build;
-            }
-            csc = plan->csc;
-        } else {
-            csc = build_csc(g, s, scratch.get());
-        }
+        if (!L->csc) L->csc = layer_csc(L, s, scratch.get());
         if (scratch) scratch->release();
-        const SampleReq req{csc.get(), d.seed, d.layer, d.fanout};
+        const SampleReq req{L->csc.get(), d.seed, d.layer, d.fanout, lists};
         L->idx = build_index(g, C, &req, s, 0, scratch.get());
-        L->csc = csc;
         if (d.agg == TAURUS_GCN_SYM) {
             // the source norms count kept out-edges: the mask in CSR order
             L->mask = L->arena.alloc<uint64_t>(std::max<int64_t>(1, ceil_div(g.e, 64)), "fanout mask");
-            sample_mask(g, *csc, d.seed, d.layer, d.fanout, L->mask, s);
+            sample_mask(g, *L->csc, d.seed, d.layer, d.fanout, L->mask, s);
         }
     } else if (plan) {
         std::lock_guard<std::mutex> lock(plan->mu);
@@ -2210,18 +2233,114 @@ static void layer_init(taurus_layer* L) {
         L->events.assign((size_t)L->nchunks * EV_PER_CHUNK, nullptr);
         for (auto& ev : L->events) ev = timing_event_acquire();
     }
-    if (s != L->s) {
-        // the layer's stream takes up the layer's memory and work from here
-        hipEvent_t ready = nullptr;
-        TAURUS_HIP(hipEventCreateWithFlags(&ready, hipEventDisableTiming));
-        const hipError_t rc1 = hipEventRecord(ready, s);
-        const hipError_t rc2 = rc1 == hipSuccess ? hipStreamWaitEvent(L->s, ready, 0) : rc1;
-        (void)hipEventDestroy(ready);  // released once the wait has been satisfied
-        TAURUS_HIP(rc2);
-        L->arena.set_stream(L->s);
-        if (L->res) L->res->arena.set_stream(L->s);
+}
+
+// Whether a layer is aggregated by destination at finalize (gather.hip)
+// instead of broadcast chunk by chunk: sampled layers in core, whose kept
+// lists are short, when a message's input row is less to read than the
+// accumulator row it would read and write (both 4 d_out bytes) and the table
+// of input rows takes at most twice the accumulators' memory, which is the
+// same line.  Not with profile (the broadcast's launches are what it times)
+// or host outputs (rows leave as they complete there).  16 floating-point
+// bits means bf16: an fp32 aggregate is three exact bf16 parts, but not
+// three fp16 ones.
+// Measured, kernel time of a layer past sampling, broadcast -> gather: 12.5M
+// vertices, 200M edges, fanout 15, 128 -> 256 bf16: 27.5 -> 6.5 ms (of which
+// the table 1.5); 3M, 48M, fanout 5, 256 -> 172: 5.0 -> 2.7 ms; 20K, 300K,
+// fanouts 10 and 5, two layers: 0.15 -> 0.06 ms.
+static bool gather_rule(const taurus_layer_desc& d) {
+    const int64_t in_bytes = (int64_t)d.d_in * (d.in_dtype == TAURUS_F32 ? 4 : 2);
+    return d.fanout > 0 && d.hbm_budget == 0 && !d.profile && !d.out_on_host && d.in_dtype != TAURUS_F16 &&
+           (d.agg == TAURUS_SAGE_MEAN || d.agg == TAURUS_GCN_SYM || d.agg == TAURUS_GIN_SUM) &&
+           d.d_in <= GATHER_MAX_K && in_bytes <= 8 * (int64_t)d.d_out;
+}
+
+// False (nothing set up but the in-edge lists) when the sample keeps every
+// edge: such a layer is the exact layer, and is broadcast like it so that
+// the two agree bit for bit.
+static bool gather_init(taurus_layer* L, hipStream_t s) {
+    const taurus_layer_desc& d = L->d;
+    const int64_t n = L->n;
+    const auto t_index = std::chrono::steady_clock::now();
+    L->csc = layer_csc(L, s, nullptr);
+    {
+        Arena tmp(s);
+        int* bad = L->arena.alloc<int>(1, "sampler flag");
+        fill_i32(bad, 1, 0, s);
+        if (!sample_lists(*L->csc, n, L->g.e, d.seed, d.layer, d.fanout, L->arena, tmp, L->lists, bad, s)) {
+            L->arena.free_ptr(bad);
+            return false;
+        }
+        L->gather_bad = bad;
+        if (n >= GATHER_ORDER_MIN)
+            L->gather_ord = gather_order(L->lists.off, n, d.fanout, L->arena, tmp, bad, 8, s);
     }
+    L->gather = true;
+    L->d_o = d.d_out;
+    L->ms_index = ms_since(t_index);
+    if (d.agg == TAURUS_GCN_SYM) {
+        L->n_out = L->arena.alloc<float>(n, "source norms");
+        gather_norms(L->lists.src, L->lists.kept, n, L->n_out, s);
+    }
+    L->list_counts = L->arena.alloc<unsigned long long>(LIST_COUNTS + 1, "list counts");
+    // weights: the aggregate's columns, then GraphSAGE's self columns
+    const bool sage = d.agg == TAURUS_SAGE_MEAN;
+    const int ld = sage ? 2 * d.d_out : d.d_out;
+    L->ncols = ld;
+    L->w_host.assign(d.weight, d.weight + (size_t)d.d_in * ld);
+    if (d.bias) L->b_host.assign(d.bias, d.bias + d.d_out);
+    std::vector<float> p32;
+    std::vector<uint16_t> p16;
+    const bool pairs = d.out_dtype != TAURUS_F32;
+    for (int h = 0; h < (sage ? 2 : 1); h++) {
+        if (d.in_dtype == TAURUS_F32) gather_pack_f32(d.weight + h * d.d_out, ld, d.d_in, d.d_out, pairs, p32);
+        else gather_pack_bf16(d.weight + h * d.d_out, ld, d.d_in, d.d_out, pairs, p16);
+    }
+    const size_t wbytes = p32.size() * 4 + p16.size() * 2;  // whole fragments: a multiple of 1 KiB
+    const size_t pbytes = wbytes + (size_t)d.d_out * 4;
+    char* stage = static_cast<char*>(pinned_staging(pbytes));
+    std::memcpy(stage, p32.empty() ? static_cast<const void*>(p16.data()) : p32.data(), wbytes);
+    float* sbias = reinterpret_cast<float*>(stage + wbytes);
+    for (int j = 0; j < d.d_out; j++) sbias[j] = d.bias ? d.bias[j] : 0.0f;
+    L->wpack_any = L->arena.alloc_bytes((int64_t)pbytes, "packed weights and bias");
+    L->bias = reinterpret_cast<float*>(static_cast<char*>(L->wpack_any) + wbytes);
+    TAURUS_HIP(hipMemcpyAsync(L->wpack_any, stage, pbytes, hipMemcpyHostToDevice, s));
+    pinned_staging_in_flight(s);
+    L->out_dev = d.out;
+    L->pushed.assign((size_t)L->nchunks, 0);
+    return true;
+}
+
+static void layer_init(taurus_layer* L) {
+    const auto t_start = std::chrono::steady_clock::now();
+    // the set-up work goes to desc.setup_stream when given (the layer's
+    // stream waits for it at the end), else to the layer's stream
+    hipStream_t s = L->d.setup_stream ? static_cast<hipStream_t>(L->d.setup_stream) : L->s;
+    L->arena.set_stream(s);
+    L->n = L->g.n;
+    L->C = L->d.chunk;
+    L->nchunks = ceil_div(L->n, L->C);
+    const taurus_plan* plan = L->d.plan;
+    if (plan && (!same_graph(plan->g, L->g) || plan->chunk != L->C))
+        fail(TAURUS_E_INVALID, "plan was built for another graph or chunk size");
+    if (!gather_rule(L->d) || !gather_init(L, s)) scatter_init(L, s, nullptr);
+    join_setup(L, s);
     L->ms_init = ms_since(t_start);  // host time; the work stays queued on the stream
+}
+
+// A gathered layer whose first chunk comes from the host is broadcast after
+// all: each chunk's messages then overlap the next chunk's copy, where a
+// gather would only start after the last copy.
+static void gather_to_scatter(taurus_layer* L) {
+    L->d.weight = L->w_host.data();
+    L->d.bias = L->b_host.empty() ? nullptr : L->b_host.data();
+    L->d.setup_stream = nullptr;
+    L->gather = false;
+    L->n_out = nullptr;
+    scatter_init(L, L->s, &L->lists);
+    L->d.weight = L->d.bias = nullptr;
+    L->w_host = {};
+    L->b_host = {};
 }
 
 // Host-resident chunk (pinned): copy it on the layer's copy stream into one
@@ -2322,8 +2441,20 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
         L->acc = L->arena.alloc<float>(L->n * (int64_t)L->d_o, "accumulators");
         L->acc_deferred = false;
     }
-    const ChunkIndex& idx = *L->idx;
     hipStream_t s = L->s;
+    if (L->gather && x_on_host && !L->table) gather_to_scatter(L);
+    if (L->gather) {
+        const int64_t row = (int64_t)L->d.d_in * (L->d.in_dtype == TAURUS_F32 ? 4 : 2);
+        if (!L->table) L->table = static_cast<char*>(L->arena.alloc_bytes(L->n * row, "input rows"));
+        if (x_on_host) x = stage_host_chunk(L, x, e - b);
+        gather_copy_rows(x, L->table + b * row, (e - b) * row, s);
+        if (x_on_host) TAURUS_HIP(hipEventRecord(L->gemm_done[(L->host_pushes - 1) & 1], s));
+        L->pushed[(size_t)k] = 1;
+        L->npushed++;
+        L->gathered = false;
+        return;
+    }
+    const ChunkIndex& idx = *L->idx;
     if (x_on_host) x = stage_host_chunk(L, x, e - b);
     // profile 1: events around every kernel; profile 2: around the scatter
     // launch only (ev[1] and ev[2])
@@ -2517,8 +2648,90 @@ static void run_gat_passes(taurus_layer* L) {
     L->gat_done = true;
 }
 
+// A gathered layer: aggregate (the destinations whose messages have all been
+// pushed), and the statistics from the lists.
+static int finalize_gather(taurus_layer* L, taurus_stats* st) {
+    hipStream_t s = L->s;
+    const taurus_layer_desc& d = L->d;
+    const bool all = L->npushed == L->nchunks;
+    const bool sage = d.agg == TAURUS_SAGE_MEAN;
+    Arena tmp(s);
+    uint8_t* ready = nullptr;
+    unsigned long long* dleft = L->list_counts + LIST_COUNTS;
+    if (!all) {
+        uint8_t* pushed = tmp.alloc<uint8_t>(L->nchunks, "pushed chunks");
+        ready = tmp.alloc<uint8_t>(L->n, "complete destinations");
+        void* stage = pinned_staging((size_t)L->nchunks);
+        std::memcpy(stage, L->pushed.data(), (size_t)L->nchunks);
+        TAURUS_HIP(hipMemcpyAsync(pushed, stage, (size_t)L->nchunks, hipMemcpyHostToDevice, s));
+        pinned_staging_in_flight(s);
+        gather_ready(L->lists.off, L->lists.src, L->n, L->C, pushed, ready, dleft, s);
+    }
+    if (L->table && !L->gathered) {
+        GatherArgs a{};
+        a.X = L->table;
+        a.n = L->n;
+        a.K = d.d_in;
+        a.off = L->lists.off;
+        a.src = L->lists.src;
+        a.W = L->wpack_any;
+        a.NBP = gather_blocks_n(d.d_out);
+        a.bias = L->bias;
+        a.norm = L->n_out;
+        a.out = L->out_dev;
+        a.d_o = d.d_out;
+        a.out_dtype = d.out_dtype;
+        a.relu = d.relu;
+        a.sage = sage ? 1 : 0;
+        a.ready = ready;
+        a.order = L->gather_ord;
+        a.nonzero = L->lists.nonzero;
+        a.pairs = d.out_dtype != TAURUS_F32 ? 1 : 0;
+        const int64_t rows = gather_partial_rows(a, d.in_dtype);
+        if (rows > 0) a.partial = tmp.alloc<float>(rows * d.d_out, "aggregate products");
+        gather_layer(a, d.in_dtype, s);
+        L->gathered = true;
+    }
+    gather_list_counts(L->lists.off, L->lists.src, L->gather_ord, L->gather_ord ? L->lists.nonzero : L->n, L->C,
+                       class_len(NCLASS - 1), PIECE_LEN, L->list_counts, s);
+    unsigned long long c[LIST_COUNTS] = {}, left = 0;
+    int bad = 0;
+    Readback rb;
+    rb.add(c, L->list_counts, LIST_COUNTS);
+    rb.add(&bad, L->gather_bad, 1);
+    if (!all) rb.add(&left, dleft, 1);
+    rb.run(s);
+    if (bad & 8) fail(TAURUS_E_DEVICE, "destination order: radix sort offset out of range");
+    if (bad) fail(TAURUS_E_INVALID, "sampler: an in-list holds repeated sources");
+    if (st) {
+        std::memset(st, 0, sizeof(*st));
+        st->n = L->n;
+        st->e = L->g.e;
+        st->messages = L->lists.kept;
+        st->self_terms = L->n;
+        st->pairs = (int64_t)c[LC_SEGMENTS] + L->n - (int64_t)c[LC_OWN];
+        if (sage) {
+            st->self_in_transform = L->n - (int64_t)c[LC_OWN];
+            st->self_fresh = st->self_last = -1;
+        }
+        st->pending_left = (int64_t)left;
+        st->completed = L->n - (int64_t)left;
+        st->chunks = L->nchunks;
+        st->chunks_pushed = L->npushed;
+        st->short_units = (int64_t)c[LC_SHORT];
+        st->wave_units = (int64_t)c[LC_WAVE];
+        st->split_segments = (int64_t)c[LC_SPLIT];
+        st->device_bytes = L->arena.peak();
+        st->ms_init = L->ms_init;
+        st->ms_index = L->ms_index;
+        st->h2d_bytes = L->h2d_bytes;
+    }
+    return left ? TAURUS_E_INCOMPLETE : TAURUS_OK;
+}
+
 static int finalize(taurus_layer* L, taurus_stats* st) {
     if (L->poisoned) fail(TAURUS_E_STATE, "layer handle is poisoned by an earlier failure");
+    if (L->gather) return finalize_gather(L, st);
     hipStream_t s = L->s;
     const ChunkIndex& idx = *L->idx;
     if (L->fix_pending) {  // the last chunk's fix-up
@@ -2903,6 +3116,10 @@ int taurus_push_chunk(taurus_layer* L, int64_t src_begin, int64_t src_end, const
         if (f.status == TAURUS_E_OOM || f.status == TAURUS_E_DEVICE || f.status == TAURUS_E_BUDGET)
             L->poisoned = true;
         return f.status;
+    } catch (const std::exception& x) {
+        L->poisoned = true;
+        set_error("internal error: %s", x.what());
+        return TAURUS_E_DEVICE;
     }
 }
 
@@ -2962,7 +3179,7 @@ int taurus_sampled_edges(taurus_layer* L, uint64_t* mask_bits_host, int64_t* n_k
             for (int64_t w = 0; w < words; w++) mask_bits_host[w] = ~0ull;
             if (L->g.e % 64) mask_bits_host[words - 1] = (1ull << (L->g.e % 64)) - 1;
         }
-        if (n_kept) *n_kept = L->idx->kept;
+        if (n_kept) *n_kept = L->gather ? L->lists.kept : L->idx->kept;
         return TAURUS_OK;
     } catch (const Failure& f) {
         return f.status;

@@ -203,7 +203,8 @@ constexpr int REG_MAX = 512;      // long lists up to this length are held in re
 
 // Where the kept in-edges go: chunk-index items at koff[v] + (position among
 // v's kept in-edges) -- key (chunk(u) << vbits | v), value u - chunk(u)*C --
-// or, when mask is set, bit (CSR position of (u, v)) of a CSR-order mask.
+// or, without keys, their sources u there; or, when mask is set, bit (CSR
+// position of (u, v)) of a CSR-order mask.
 struct SampleOut {
     uint64_t* keys;
     uint32_t* vals;
@@ -230,6 +231,8 @@ __device__ inline void emit_item(const SampleOut& o, int64_t v, uint32_t u, int6
             else hi = mid;
         }
         atomicOr(&o.mask[lo >> 6], 1ull << (lo & 63));
+    } else if (!o.keys) {
+        o.vals[at] = u;
     } else {
         const uint32_t cu = u / (uint32_t)o.C;  // u < 2^31 and C < 2^31
         // not the destination's first flush: a chunk after the earlier of
@@ -245,7 +248,7 @@ __device__ inline void emit_kept(const SampleOut& o, int64_t v, uint32_t u, int6
     emit_item(o, v, u, o.mask ? 0 : o.koff[v] + pos, pos == 0, fcu);
 }
 
-// Lists of 1 .. min(k, LIGHT_MAX) in-edges, kept whole, and the
+// Lists of 1 .. min(k, whole_max) in-edges, kept whole, and the
 // destinations whose lists need ranking (k < d_in <= LIGHT_MAX) noted in
 // rank_list.  A wave takes 64 consecutive destinations, a lane each; their
 // kept in-edges are copied in-edge-parallel (item t of the wave's run goes
@@ -253,7 +256,7 @@ __device__ inline void emit_kept(const SampleOut& o, int64_t v, uint32_t u, int6
 // read and the items written contiguously.
 __global__ __launch_bounds__(256) void k_sample_short(const int64_t* __restrict__ in_off,
                                                       const int32_t* __restrict__ in_src, int64_t n, int k,
-                                                      SampleOut o, int32_t* __restrict__ rank_list,
+                                                      int whole_max, SampleOut o, int32_t* __restrict__ rank_list,
                                                       unsigned int* __restrict__ rank_count) {
     // destinations to rank wait in a per-wave LDS buffer and leave it 64 at
     // a time, so the shared list count takes one atomic per 64 of them
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(256) void k_sample_short(const int64_t* __restrict_
     const uint64_t lt = (1ull << lane) - 1ull;
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int64_t cmax = min((int64_t)k, (int64_t)LIGHT_MAX);
+    const int64_t cmax = min(k, whole_max);
     auto flush = [&](int cnt) {  // the first cnt buffered entries to the list
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -551,8 +554,8 @@ static void sample_pass(const Csc& csc, int64_t n, uint64_t seed, int layer, int
     unsigned int* rank_count = tmp.alloc<unsigned int>(1, "short lists to rank: count");
     fill_i32(reinterpret_cast<int32_t*>(rank_count), 1, 0, s);
     const int64_t grid_short = std::min<int64_t>(ceil_div(n, 256), (int64_t)cus * 32);
-    k_sample_short<<<(unsigned)std::max<int64_t>(1, grid_short), 256, 0, s>>>(csc.in_off, csc.in_src, n, k, o,
-                                                                             rank_list, rank_count);
+    k_sample_short<<<(unsigned)std::max<int64_t>(1, grid_short), 256, 0, s>>>(csc.in_off, csc.in_src, n, k, LIGHT_MAX,
+                                                                             o, rank_list, rank_count);
     TAURUS_CHECK_LAUNCH();
     if (k < LIGHT_MAX) {  // else every list of at most LIGHT_MAX in-edges is kept whole
         k_sample_light<<<(unsigned)cus * 32, 256, 0, s>>>(csc.in_off, csc.in_src, rank_list, rank_count, seed, layer,
@@ -573,37 +576,103 @@ static void sample_pass(const Csc& csc, int64_t n, uint64_t seed, int layer, int
     }
 }
 
-// kept per destination, min(d_in(v), k)
-__global__ void k_sample_counts(const int64_t* __restrict__ in_off, int64_t n, int k, int32_t* __restrict__ m) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n) m[v] = (int32_t)min(in_off[v + 1] - in_off[v], (int64_t)k);
+// kept per destination, min(d_in(v), k), and the number of destinations
+// that keep any (nonzero, may be null: one atomic per workgroup of a bounded
+// grid)
+__global__ __launch_bounds__(256) void k_sample_counts(const int64_t* __restrict__ in_off, int64_t n, int k,
+                                                       int32_t* __restrict__ m,
+                                                       unsigned long long* __restrict__ nonzero) {
+    __shared__ unsigned int part[4];
+    unsigned int c = 0;
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
+        const int x = (int)min(in_off[v + 1] - in_off[v], (int64_t)k);
+        m[v] = x;
+        c += x > 0;
+    }
+    if (!nonzero) return;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(nonzero, (unsigned long long)(part[0] + part[1] + part[2] + part[3]));
+}
+static unsigned count_blocks(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), 4096)); }
+
+// koff (n + 1, from key_arena) = the exclusive scan of min(d_in, k); m[v] =
+// min(d_in(v), k); returns the number kept
+// (and, when asked, the destinations that keep any)
+static int64_t sample_offsets(const Csc& csc, int64_t n, int k, Arena& off_arena, Arena& tmp, int32_t* m,
+                              int64_t** koff, hipStream_t s, int64_t* nonzero = nullptr) {
+    if (k < 1 || k > FANOUT_MAX) fail(TAURUS_E_INVALID, "fanout %d outside [1, %d]", k, FANOUT_MAX);
+    *koff = off_arena.alloc<int64_t>(n + 1, "kept before each destination");
+    unsigned long long* dnz = nullptr;
+    if (nonzero) {
+        dnz = tmp.alloc<unsigned long long>(1, "destinations with kept in-edges");
+        fill_i32(reinterpret_cast<int32_t*>(dnz), 2, 0, s);
+    }
+    k_sample_counts<<<count_blocks(n), 256, 0, s>>>(csc.in_off, n, k, m, dnz);
+    TAURUS_CHECK_LAUNCH();
+    scan_i32_to_i64(m, *koff, n, true, tmp, s);
+    int64_t kept = 0;
+    Readback rb;
+    rb.add(&kept, *koff + n, 1);
+    if (nonzero) rb.add(reinterpret_cast<unsigned long long*>(nonzero), dnz, 1);
+    rb.run(s);
+    return kept;
 }
 
-int64_t sample_items(const Csc& csc, int64_t n, uint64_t seed, int layer, int k, int64_t C, int vbits,
-                     Arena& key_arena, Arena& val_arena, SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad,
-                     hipStream_t s) {
-    if (k < 1 || k > FANOUT_MAX) fail(TAURUS_E_INVALID, "fanout %d outside [1, %d]", k, FANOUT_MAX);
-    int64_t* koff = key_arena.alloc<int64_t>(n + 1, "kept before each destination");
-    k_sample_counts<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(csc.in_off, n, k, m);
-    TAURUS_CHECK_LAUNCH();
-    scan_i32_to_i64(m, koff, n, true, key_arena, s);
-    int64_t kept = 0;
-    {
-        Readback rb;
-        rb.add(&kept, koff + n, 1);
-        rb.run(s);
-    }
+static void item_buffers(int64_t kept, Arena& key_arena, Arena& val_arena, SortBuffers& sb) {
     const int64_t k1 = std::max<int64_t>(kept, 1);
     sb.keys[0] = key_arena.alloc<uint64_t>(k1, "index keys");
     sb.keys[1] = key_arena.alloc<uint64_t>(k1, "index keys (ping-pong)");
     sb.vals[0] = val_arena.alloc<uint32_t>(k1, "index values");
     sb.vals[1] = val_arena.alloc<uint32_t>(k1, "index values (ping-pong)");
     sb.cur = 0;
+}
+
+int64_t sample_items(const Csc& csc, int64_t n, uint64_t seed, int layer, int k, int64_t C, int vbits,
+                     Arena& key_arena, Arena& val_arena, SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad,
+                     hipStream_t s) {
+    int64_t* koff = nullptr;
+    const int64_t kept = sample_offsets(csc, n, k, key_arena, key_arena, m, &koff, s);
+    item_buffers(kept, key_arena, val_arena, sb);
     if (kept > 0)
         sample_pass(csc, n, seed, layer, k,
                     SampleOut{sb.keys[0], sb.vals[0], koff, C, vbits, nullptr, nullptr, nullptr, bad, first_chunk},
                     key_arena, s);
     return kept;
+}
+
+bool sample_lists(const Csc& csc, int64_t n, int64_t e, uint64_t seed, int layer, int k, Arena& arena, Arena& tmp,
+                  SampleLists& out, int* bad, hipStream_t s) {
+    int32_t* m = tmp.alloc<int32_t>(n, "kept per destination");
+    out.kept = sample_offsets(csc, n, k, arena, tmp, m, &out.off, s, &out.nonzero);
+    if (out.kept == e) {
+        arena.free_ptr(out.off);
+        out = SampleLists{};
+        return false;
+    }
+    out.src = arena.alloc<uint32_t>(std::max<int64_t>(out.kept, 1), "kept sources");
+    if (out.kept > 0)
+        sample_pass(csc, n, seed, layer, k,
+                    SampleOut{nullptr, out.src, out.off, 1, 1, nullptr, nullptr, nullptr, bad, nullptr}, tmp, s);
+    return true;
+}
+
+int64_t list_items(const SampleLists& l, int64_t n, int64_t C, int vbits, Arena& key_arena, Arena& val_arena,
+                   SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad, hipStream_t s) {
+    item_buffers(l.kept, key_arena, val_arena, sb);
+    k_sample_counts<<<count_blocks(n), 256, 0, s>>>(l.off, n, FANOUT_MAX, m, nullptr);
+    TAURUS_CHECK_LAUNCH();
+    if (l.kept > 0) {
+        // every list is copied whole: a kept list is at most FANOUT_MAX long
+        k_sample_short<<<(unsigned)std::min<int64_t>(ceil_div(n, 256), 8192), 256, 0, s>>>(
+            l.off, reinterpret_cast<const int32_t*>(l.src), n, FANOUT_MAX, FANOUT_MAX,
+            SampleOut{sb.keys[0], sb.vals[0], l.off, C, vbits, nullptr, nullptr, nullptr, bad, first_chunk}, nullptr,
+            nullptr);
+        TAURUS_CHECK_LAUNCH();
+    }
+    return l.kept;
 }
 
 void sample_mask(const taurus_graph& g, const Csc& csc, uint64_t seed, int layer, int k, uint64_t* mask,

@@ -1,0 +1,217 @@
+"""Sampled layers kept in core (aggregated by destination at finalize) against
+a 64-bit evaluation of the edges the layer says it keeps: widths at the edges
+of the k-blocks and column groups, every family and type, lists of 0 to k
+in-edges, partial pushes, host-fed chunks, values that are not finite.
+
+Tolerance: fp32 outputs 2e-5 of the output's RMS per element -- a sum of at
+most k = 64 messages and 256 products in fp32 errs by at most
+(64 + 3 * 256) * 2^-24 = 5e-5 of the sum of magnitudes, and a tenth of that
+with rounding of either sign; 16-bit outputs one rounding, 2^-8 of the value.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SAGE, GCN, GIN = 0, 1, 2
+F32, BF16, F16 = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _graph(torch, n, e, seed):
+    """Distinct pairs, no loops; vertex 0 has many in-edges, the last none."""
+    import paper_2607_17374_amd as T
+    rng = np.random.default_rng(seed)
+    u = np.concatenate([rng.integers(0, n, e), np.arange(1, n)])
+    v = np.concatenate([rng.integers(0, n - 1, e), np.zeros(n - 1, np.int64)])
+    key = np.unique((u * n + v)[u != v])
+    src, dst = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    row_off, col_dst = T.build_csr(n, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda())
+    return src, dst, row_off, col_dst
+
+
+def _reference(agg, n, src, dst, words, x, W, b, relu, d_out):
+    keep = np.unpackbits(words.view(np.uint8), bitorder="little")[:len(src)].astype(bool)
+    order = np.lexsort((dst, src))              # CSR order
+    u, v = src[order][keep], dst[order][keep]
+    d_in = np.bincount(v, minlength=n)
+    s = np.zeros((n, x.shape[1]))
+    if agg == SAGE:
+        np.add.at(s, v, x[u])
+        z = (s / np.maximum(d_in, 1)[:, None]) @ W[:, :d_out] + x @ W[:, d_out:]
+    elif agg == GCN:
+        no = 1 / np.sqrt(np.bincount(u, minlength=n) + 1.0)
+        np.add.at(s, v, x[u] * no[u][:, None])
+        z = ((s + x * no[:, None]) / np.sqrt(d_in + 1.0)[:, None]) @ W
+    else:
+        np.add.at(s, v, x[u])
+        z = (s + x) @ W
+    z = z + b
+    return np.maximum(z, 0) if relu else z
+
+
+def _layer(torch, n, row_off, col_dst, agg, d_in, d_out, dtype, out_dtype, k, seed=3, chunk=192, relu=True, **more):
+    import paper_2607_17374_amd as T
+    rng = np.random.default_rng(seed)
+    td = [torch.float32, torch.bfloat16, torch.float16]
+    W = (rng.standard_normal((d_in, d_out * (2 if agg == SAGE else 1))) / np.sqrt(d_in)).astype(np.float32)
+    b = rng.uniform(-0.1, 0.1, d_out).astype(np.float32)
+    x = torch.from_numpy(rng.standard_normal((n, d_in)).astype(np.float32)).to(td[dtype])
+    Wx = torch.from_numpy(W).to(td[dtype]).double().numpy() if dtype else W.astype(np.float64)
+    out = torch.full((n, d_out), -7.0, dtype=td[out_dtype], device="cuda")
+    L = T.Layer(n, row_off, col_dst, agg=agg, d_in=d_in, d_out=d_out, weight_cat=W, bias=b, out=out, in_dtype=dtype,
+                out_dtype=out_dtype, relu=relu, fanout=k, layer=1, seed=seed, chunk=chunk, **more)
+    return L, x, Wx, b, out
+
+
+def _check(out, z, out_dtype):
+    y = out.double().cpu().numpy()
+    rms = np.sqrt(np.mean(z * z))
+    tol = 2e-5 * (np.abs(z) + rms) + (2.0 ** -8 * np.abs(z) if out_dtype else 0)
+    assert np.all(np.abs(y - z) <= tol), float(np.max(np.abs(y - z) / (np.abs(z) + rms)))
+
+
+CASES = [(agg, d_in, d_out, dt, od, k)
+         for agg, d_in, d_out, dt, od, k in [
+             (SAGE, 128, 256, BF16, BF16, 15), (SAGE, 256, 172, BF16, F32, 5), (SAGE, 8, 4, BF16, F32, 1),
+             (SAGE, 104, 128, BF16, F16, 10), (SAGE, 64, 16, F32, F32, 7), (SAGE, 4, 12, F32, BF16, 3),
+             (SAGE, 256, 200, F32, F32, 64), (SAGE, 132, 260, F32, F32, 10), (SAGE, 72, 1024, BF16, BF16, 4),
+             (GCN, 128, 64, BF16, F32, 10), (GCN, 68, 44, F32, F32, 15), (GCN, 200, 132, BF16, BF16, 25),
+             (GIN, 64, 64, BF16, F32, 5), (GIN, 100, 300, F32, F16, 10), (GIN, 248, 68, BF16, F32, 64),
+             (SAGE, 264, 256, BF16, F32, 5), (SAGE, 128, 64, F16, F32, 5), (GCN, 256, 16, F32, F32, 5)]]
+
+
+@pytest.mark.parametrize("agg,d_in,d_out,dt,od,k", CASES)
+@pytest.mark.parametrize("n", [1000, 1025])
+def test_sampled_layer(torch_cuda, n, agg, d_in, d_out, dt, od, k):
+    torch = torch_cuda
+    print(f"gather n={n} agg={agg} {d_in}->{d_out} dt={dt}/{od} k={k}", flush=True)
+    src, dst, row_off, col_dst = _graph(torch, n, 6 * n, 1)
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, d_in, d_out, dt, od, k)
+    L.push_all(x.cuda())
+    st = L.finalize()
+    words, kept = L.sampled_edges()
+    L.destroy()
+    assert st["completed"] == n and st["messages"] == kept
+    _check(out, _reference(agg, n, src, dst, words, x.double().numpy(), W, b, True, d_out), od)
+
+
+def test_partial_pushes_write_complete_rows_only(torch_cuda):
+    """finalize with chunks missing: INCOMPLETE, the rows whose messages have
+    all arrived written, the others untouched; then the rest, in any order."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, chunk = 1000, 192
+    src, dst, row_off, col_dst = _graph(torch, n, 3000, 2)
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, SAGE, 32, 16, F32, F32, 3, chunk=chunk, relu=False)
+    xd = x.cuda()
+    with pytest.raises(T.TaurusError) as ex:
+        L.finalize()
+    assert ex.value.status == -5 and bool((out == -7.0).all())
+    for k in (4, 0, 2):
+        L.push_chunk(k * chunk, min(n, k * chunk + chunk), xd[k * chunk:k * chunk + chunk])
+    with pytest.raises(T.TaurusError) as ex:
+        L.finalize()
+    assert ex.value.status == -5
+    words, _ = L.sampled_edges()
+    z = _reference(SAGE, n, src, dst, words, x.double().numpy(), W, b, False, 16)
+    keep = np.unpackbits(words.view(np.uint8), bitorder="little")[:len(src)].astype(bool)
+    order = np.lexsort((dst, src))
+    u, v = src[order][keep], dst[order][keep]
+    done = np.isin(np.arange(n) // chunk, (0, 2, 4))
+    done[v[~np.isin(u // chunk, (0, 2, 4))]] = False
+    assert 0 < done.sum() < n
+    y = out.cpu().numpy()
+    assert np.all(y[~done] == -7.0)
+    _check(out[torch.from_numpy(done).cuda()], z[done], F32)
+    for k in (3, 1, 5):
+        L.push_chunk(k * chunk, min(n, k * chunk + chunk), xd[k * chunk:min(n, k * chunk + chunk)])
+    st = L.finalize()
+    assert st["completed"] == n and st["pending_left"] == 0
+    first = out.clone()
+    assert L.finalize()["completed"] == n and torch.equal(out, first)   # a second finalize changes nothing
+    L.destroy()
+    _check(out, z, F32)
+
+
+@pytest.mark.parametrize("agg", [SAGE, GCN])
+@pytest.mark.parametrize("first_on_host", [True, False])
+def test_host_fed_chunks(torch_cuda, agg, first_on_host):
+    """A layer fed from pinned memory is broadcast chunk by chunk; one whose
+    first chunk was on the device keeps gathering.  Statistics that describe
+    the sample are the same."""
+    torch = torch_cuda
+    n, chunk = 1025, 192
+    src, dst, row_off, col_dst = _graph(torch, n, 6000, 3)
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, 64, 48, BF16, F32, 6, chunk=chunk)
+    xh, xd = x.pin_memory(), x.cuda()
+    for i, c in enumerate(range(0, n, chunk)):
+        on_host = first_on_host or i % 2 == 1
+        L.push_chunk(c, min(n, c + chunk), (xh if on_host else xd)[c:min(n, c + chunk)])
+    st = L.finalize()
+    words, kept = L.sampled_edges()
+    L.destroy()
+    _check(out, _reference(agg, n, src, dst, words, x.double().numpy(), W, b, True, 48), F32)
+    L, _, _, _, out2 = _layer(torch, n, row_off, col_dst, agg, 64, 48, BF16, F32, 6, chunk=chunk)
+    L.push_all(xd)
+    st2 = L.finalize()
+    L.destroy()
+    for key in ("messages", "pairs", "short_units", "wave_units", "split_segments", "completed", "pending_left",
+                "chunks_pushed", "self_in_transform"):
+        assert st[key] == st2[key], key
+
+
+def test_statistics_match_the_broadcast(torch_cuda):
+    """Counts of a gathered layer equal those of the same layer's chunk index
+    (a profiled layer builds it); k = 512 gives a segment of several pieces."""
+    torch = torch_cuda
+    n = 1025
+    src, dst, row_off, col_dst = _graph(torch, n, 6000, 4)
+    for k, chunk in ((6, 192), (512, 1025)):
+        got = []
+        for profile in (0, 1):
+            L, x, _, _, _ = _layer(torch, n, row_off, col_dst, SAGE, 64, 48, BF16, F32, k, chunk=chunk,
+                                   profile=profile)
+            L.push_all(x.cuda())
+            got.append(L.finalize())
+            L.destroy()
+        for key in ("messages", "pairs", "short_units", "wave_units", "split_segments", "completed",
+                    "self_in_transform"):
+            assert got[0][key] == got[1][key], (k, key)
+        assert k < 512 or got[0]["split_segments"] == 1
+
+
+def test_values_that_are_not_finite(torch_cuda):
+    """An infinite input reaches exactly the rows it is sent to, as infinity
+    of the product's sign, and large finite means do not overflow the parts."""
+    torch = torch_cuda
+    n = 1000
+    src, dst, row_off, col_dst = _graph(torch, n, 4000, 5)
+    for bad in (np.inf, 3.0e38):
+        L, x, W, b, out = _layer(torch, n, row_off, col_dst, SAGE, 64, 16, BF16, F32, 4, relu=False)
+        W[:] = np.abs(W)
+        import paper_2607_17374_amd as T
+        L.destroy()
+        Wp = np.abs((np.random.default_rng(3).standard_normal((64, 32)) / 8).astype(np.float32)) / 64
+        x = x.clone()
+        x[7, 3] = bad
+        L = T.Layer(n, row_off, col_dst, agg=SAGE, d_in=64, d_out=16, weight_cat=Wp, bias=b, out=out, in_dtype=BF16,
+                    out_dtype=F32, fanout=4, layer=1, seed=3, chunk=192)
+        L.push_all(x.cuda())
+        L.finalize()
+        words, _ = L.sampled_edges()
+        L.destroy()
+        z = _reference(SAGE, n, src, dst, words, x.double().numpy(),
+                       torch.from_numpy(Wp).bfloat16().double().numpy(), b, False, 16)
+        y = out.double().cpu().numpy()
+        assert np.array_equal(np.isinf(y), np.isinf(z)) and np.isfinite(y).sum() == np.isfinite(z).sum()
+        fin = np.isfinite(z)
+        rms = np.sqrt(np.mean(z[fin & (np.abs(z) < 1e30)] ** 2))
+        assert np.all(np.abs(y[fin] - z[fin]) <= 2e-5 * (np.abs(z[fin]) + rms))
