@@ -113,67 +113,177 @@ __global__ void k_label_jump(const uint32_t* __restrict__ order, int64_t n, int3
     }
 }
 
-// size[l] = vertices labelled l.  Lanes of a wave with the same label add
-// once (a giant component would otherwise put nearly every vertex's atomic
-// on one counter): the first remaining lane's label is matched by ballot,
-// that lane adds the matches, and the rest go round again.
-__global__ void k_tree_sizes(const int32_t* __restrict__ label, int64_t n, int32_t* __restrict__ size) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// size[l] = vertices labelled l.  One counter taking an atomic from every wave
+// costs 12 ns each, so what is common is added up first: label 0 (the tree of
+// the first root, with degree keys nearly always the largest) per workgroup
+// of a bounded grid, and other labels that lanes of a wave share by rounds of
+// ballots.  A root other than the first adds itself alone (it has its own
+// counter; a graph of many isolated vertices would otherwise go round up to
+// 64 times a wave).  1M vertices, 20M edges: 190 us with rounds alone,
+// 12 us this way.
+constexpr int TS_BLOCKS = 512;
+__global__ __launch_bounds__(256) void k_tree_sizes(const int32_t* __restrict__ label,
+                                                    const int32_t* __restrict__ rank, int64_t n,
+                                                    int32_t* __restrict__ size) {
+    __shared__ int part[4];
     const int lane = threadIdx.x & 63;
-    const int32_t l = v < n ? label[v] : -1;
-    uint64_t left = __ballot(v < n);
-    while (left) {  // uniform over the wave
-        const int lead = __builtin_ctzll(left);
-        const int32_t ll = __shfl(l, lead);
-        const uint64_t same = __ballot(v < n && l == ll);
-        if (lane == lead) atomicAdd(&size[ll], (int)__popcll(same));
-        left &= ~same;
+    int first = 0;  // this wave's vertices labelled 0
+    for (int64_t v0 = (int64_t)blockIdx.x * 256; v0 < n; v0 += (int64_t)gridDim.x * 256) {  // uniform
+        const int64_t v = v0 + threadIdx.x;
+        const int32_t l = v < n ? label[v] : -1;
+        first += (int)__popcll(__ballot(l == 0));
+        const bool root = l > 0 && rank[v] == l;
+        if (root) atomicAdd(&size[l], 1);
+        uint64_t left = __ballot(l > 0 && !root);
+        while (left) {  // uniform over the wave
+            const int lead = __builtin_ctzll(left);
+            const int32_t ll = __shfl(l, lead);
+            const uint64_t same = __ballot(!root && l == ll) & left;
+            if (lane == lead) atomicAdd(&size[ll], (int)__popcll(same));
+            left &= ~same;
+        }
     }
+    if (lane == 0) part[threadIdx.x >> 6] = first;
+    __syncthreads();
+    const int sum = part[0] + part[1] + part[2] + part[3];
+    if (threadIdx.x == 0 && sum) atomicAdd(&size[0], sum);
 }
 
-// roots: pos = the first slot of their tree; they form the first frontier
-__global__ void k_roots(const int32_t* __restrict__ label, const int32_t* __restrict__ rank,
-                        const int64_t* __restrict__ off, int64_t n, int32_t* __restrict__ pos,
-                        int32_t* __restrict__ next, int32_t* __restrict__ frontier,
-                        unsigned long long* __restrict__ count) {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    const int32_t r = rank[v];
-    const bool root = label[v] == r;
+// roots, in rank order: the vertex of rank r is one when its label is r.  A
+// root takes the first slot of its tree; those with a search list form the
+// first frontier, in position order (flag, then k_root_frontier).
+__global__ void k_roots(const int32_t* __restrict__ label, const uint32_t* __restrict__ order,
+                        const int64_t* __restrict__ off, const int64_t* __restrict__ list_off, int64_t n,
+                        int32_t* __restrict__ pos, int32_t* __restrict__ next, int32_t* __restrict__ flag) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= n) return;
+    const uint32_t v = order[r];
+    const bool root = label[v] == (int32_t)r;
     if (root) {
         pos[v] = (int32_t)off[r];
         next[r] = 1;
     }
-    const unsigned long long at = wave_append(root, count);
-    if (root) frontier[at] = (int32_t)v;
+    flag[r] = root && list_off[v + 1] > list_off[v] ? 1 : 0;
+}
+__global__ void k_root_frontier(const uint32_t* __restrict__ order, const int32_t* __restrict__ flag,
+                                const int64_t* __restrict__ at, int64_t n, int32_t* __restrict__ frontier) {
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < n && flag[r]) frontier[at[r]] = (int32_t)order[r];
 }
 
-// One wave per frontier vertex x: each unvisited neighbour w (x's search
-// list) in x's tree records the smallest claiming position and is listed once.
-__global__ __launch_bounds__(256) void k_expand(const int32_t* __restrict__ frontier, int64_t nf,
-                                                const int64_t* __restrict__ in_off,
-                                                const int32_t* __restrict__ in_src,
-                                                const int32_t* __restrict__ label, const int32_t* __restrict__ pos,
-                                                int32_t* __restrict__ claim, int32_t* __restrict__ listed,
-                                                int32_t* __restrict__ cand, unsigned long long* __restrict__ count) {
-    const int lane = threadIdx.x & 63;
-    const int64_t f = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (f >= nf) return;
-    const int32_t x = frontier[f];
-    const int32_t px = pos[x], lx = label[x];
-    for (int64_t k = in_off[x] + lane; k < in_off[x + 1]; k += 64) {
-        const int32_t w = in_src[k];
-        bool add = false;
-        if (pos[w] < 0 && label[w] == lx) {
-            atomicMin(&claim[w], px);
-            add = atomicExch(&listed[w], 1) == 0;
-        }
-        const unsigned long long at = wave_append(add, count);
-        if (add) cand[at] = w;
+// Expansion of a level.  Each unvisited neighbour w (x's search list) in
+// frontier vertex x's tree records the smallest claiming frontier index (the
+// frontier is in position order) and is listed by its first claim.  A wave
+// takes a frontier vertex at a time; lists of more than XP_PIECE entries are
+// cut into pieces of that many, which k_expand notes and k_expand_pieces
+// takes (a wave walking a hub's list alone, 64 entries at a time, held the
+// level up: 4.7 of 7.2 ms of kernel time at 1M vertices and 20M edges, now
+// 0.62).  Candidates gather in LDS and leave XP_FLUSH or more at a time, with
+// one atomic on the shared count each.
+constexpr int XP_THREADS = 256, XP_PIECE = 1024, XP_BUF = 2048, XP_FLUSH = XP_BUF - XP_THREADS;
+
+struct Candidates {
+    int32_t* buf;            // LDS, XP_BUF
+    unsigned int* n;         // LDS
+    int32_t* list;
+    unsigned long long* count;
+};
+// the whole workgroup: write the buffered candidates out when they are many
+// (or at the end, any)
+__device__ inline void flush_candidates(const Candidates& c, unsigned long long* base, bool last) {
+    __syncthreads();
+    const unsigned int m = *c.n;
+    __syncthreads();  // every wave has read it before any adds more
+    if (m > (last ? 0u : (unsigned)XP_FLUSH)) {  // uniform over the workgroup
+        if (threadIdx.x == 0) *base = atomicAdd(c.count, (unsigned long long)m);
+        __syncthreads();
+        for (unsigned int i = threadIdx.x; i < m; i += XP_THREADS) c.list[*base + i] = c.buf[i];
+        __syncthreads();
+        if (threadIdx.x == 0) *c.n = 0;
+        __syncthreads();
     }
 }
+// one entry of a list for a lane (valid): claim w for frontier index f
+__device__ inline void expand_entry(bool valid, int32_t w, int32_t f, int32_t lx, const int32_t* __restrict__ label,
+                                    const int32_t* __restrict__ pos, int32_t* __restrict__ claim,
+                                    const Candidates& c) {
+    const bool open = valid && pos[w] < 0 && label[w] == lx && claim[w] > f;
+    const bool add = open && atomicMin(&claim[w], f) == INT32_MAX;
+    const unsigned int at = wave_append(add, c.n);
+    if (add) c.buf[at] = w;
+}
 
-// key (claiming position, rank): the order the queue appends the level in
+__global__ __launch_bounds__(XP_THREADS) void k_expand(
+    const int32_t* __restrict__ frontier, int64_t nf, const int64_t* __restrict__ list_off,
+    const int32_t* __restrict__ list_adj, const int32_t* __restrict__ label, const int32_t* __restrict__ pos,
+    int32_t* __restrict__ claim, int2* __restrict__ pieces, unsigned long long* __restrict__ piece_count,
+    int32_t* __restrict__ cand, unsigned long long* __restrict__ count) {
+    __shared__ int32_t buf[XP_BUF];
+    __shared__ unsigned int nbuf;
+    __shared__ unsigned long long base;
+    if (threadIdx.x == 0) nbuf = 0;
+    __syncthreads();
+    const Candidates c{buf, &nbuf, cand, count};
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int NW = XP_THREADS / 64;
+    for (int64_t f0 = (int64_t)blockIdx.x * NW; f0 < nf; f0 += (int64_t)gridDim.x * NW) {  // uniform over the workgroup
+        const int64_t f = f0 + wave;
+        int64_t a = 0;
+        int len = 0, lx = 0;
+        if (f < nf) {
+            const int32_t x = frontier[f];
+            a = list_off[x];
+            const int64_t d = list_off[x + 1] - a;
+            lx = label[x];
+            if (d > XP_PIECE) {
+                const int64_t np = (d + XP_PIECE - 1) / XP_PIECE;
+                unsigned long long at = 0;
+                if (lane == 0) at = atomicAdd(piece_count, (unsigned long long)np);
+                at = __shfl(at, 0);
+                for (int64_t q = lane; q < np; q += 64) pieces[at + q] = make_int2((int)f, (int)q);
+            } else {
+                len = (int)d;
+            }
+        }
+        // XP_PIECE entries at most: four rounds of 256 a workgroup pass, each
+        // adding at most XP_THREADS candidates
+        for (int k0 = 0; k0 < XP_PIECE; k0 += 64) {
+            if (__syncthreads_or(k0 < len) == 0) break;  // uniform
+            const bool valid = k0 + lane < len;
+            expand_entry(valid, valid ? list_adj[a + k0 + lane] : 0, (int32_t)f, lx, label, pos, claim, c);
+            flush_candidates(c, &base, false);
+        }
+    }
+    flush_candidates(c, &base, true);
+}
+
+__global__ __launch_bounds__(XP_THREADS) void k_expand_pieces(
+    const int32_t* __restrict__ frontier, const int2* __restrict__ pieces,
+    const unsigned long long* __restrict__ piece_count, const int64_t* __restrict__ list_off,
+    const int32_t* __restrict__ list_adj, const int32_t* __restrict__ label, const int32_t* __restrict__ pos,
+    int32_t* __restrict__ claim, int32_t* __restrict__ cand, unsigned long long* __restrict__ count) {
+    __shared__ int32_t buf[XP_BUF];
+    __shared__ unsigned int nbuf;
+    __shared__ unsigned long long base;
+    if (threadIdx.x == 0) nbuf = 0;
+    __syncthreads();
+    const Candidates c{buf, &nbuf, cand, count};
+    const int64_t np = (int64_t)*piece_count;
+    for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {  // uniform over the workgroup
+        const int2 q = pieces[p];
+        const int32_t x = frontier[q.x];
+        const int32_t lx = label[x];
+        const int64_t a = list_off[x] + (int64_t)q.y * XP_PIECE, e = min(a + XP_PIECE, list_off[x + 1]);
+        for (int64_t k0 = a; k0 < e; k0 += XP_THREADS) {    // uniform
+            const int64_t k = k0 + threadIdx.x;
+            expand_entry(k < e, k < e ? list_adj[k] : 0, q.x, lx, label, pos, claim, c);
+            flush_candidates(c, &base, false);
+        }
+    }
+    flush_candidates(c, &base, true);
+}
+
+// key (claiming frontier index, rank): the order the queue appends the level in
 __global__ void k_level_keys(const int32_t* __restrict__ cand, int64_t nc, const int32_t* __restrict__ claim,
                              const int32_t* __restrict__ rank, int rbits, uint64_t* __restrict__ keys,
                              uint32_t* __restrict__ vals) {
@@ -231,6 +341,7 @@ struct Search {
     int64_t reach_e;
     const int64_t* list_off;  // a dequeued x appends from list_adj[list_off[x] .. list_off[x+1]);
     const int32_t* list_adj;  // its length is the degree of the key
+    int64_t list_e;           // entries of list_adj
     bool ascending;           // key: degree ascending (else descending), then ID ascending
     bool reverse;             // new_of_old = n - 1 - visit position
 };
@@ -277,7 +388,7 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
     // 3. tree offsets, roots
     int32_t* size = tmp.alloc<int32_t>(n, "tree sizes");
     fill_i32(size, n, 0, s);
-    k_tree_sizes<<<blocks(n), T, 0, s>>>(label, n, size);
+    k_tree_sizes<<<std::min<unsigned>(blocks(n), TS_BLOCKS), T, 0, s>>>(label, rank, n, size);
     TAURUS_CHECK_LAUNCH();
     int64_t* off = tmp.alloc<int64_t>(n + 1, "tree offsets");
     scan_i32_to_i64(size, off, n, true, tmp, s);
@@ -285,36 +396,54 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
     fill_i32(pos, n, -1, s);
     int32_t* next = tmp.alloc<int32_t>(n, "next free slot per tree");
     fill_i32(next, n, 0, s);
-    int32_t* claim = tmp.alloc<int32_t>(n, "claiming positions");
+    int32_t* claim = tmp.alloc<int32_t>(n, "claims");
     fill_i32(claim, n, INT32_MAX, s);
-    int32_t* listed = tmp.alloc<int32_t>(n, "listed flags");
-    fill_i32(listed, n, 0, s);
     int32_t* start = tmp.alloc<int32_t>(n, "run starts");
     int32_t* frontier = tmp.alloc<int32_t>(n, "frontier");
     int32_t* cand = tmp.alloc<int32_t>(n, "candidates");
-    unsigned long long* count = tmp.alloc<unsigned long long>(1, "count");
-    fill_i32(reinterpret_cast<int32_t*>(count), 2, 0, s);
-    k_roots<<<blocks(n), T, 0, s>>>(label, rank, off, n, pos, next, frontier, count);
-    TAURUS_CHECK_LAUNCH();
-    unsigned long long nf = 0;
+    // [0] candidates, [1] pieces of the level's long lists; a list's pieces
+    // are at most twice its entries / XP_PIECE
+    unsigned long long* count = tmp.alloc<unsigned long long>(2, "counts");
+    int2* pieces = tmp.alloc<int2>(2 * (sp.list_e / XP_PIECE) + 1, "list pieces");
+    int64_t nf = 0, nroots = 0;
     {
+        int32_t* rflag = cand;                      // free until the first level
+        int64_t* rat = tmp.alloc<int64_t>(n + 1, "root positions");
+        k_roots<<<blocks(n), T, 0, s>>>(label, order, off, sp.list_off, n, pos, next, rflag);
+        TAURUS_CHECK_LAUNCH();
+        scan_i32_to_i64(rflag, rat, n, true, tmp, s);
+        k_root_frontier<<<blocks(n), T, 0, s>>>(order, rflag, rat, n, frontier);
+        TAURUS_CHECK_LAUNCH();
+        int64_t* rsum = tmp.alloc<int64_t>(n + 1, "root counts");
+        scan_i32_to_i64(next, rsum, n, true, tmp, s);
         Readback rb;
-        rb.add(&nf, count, 1);
+        rb.add(&nf, rat + n, 1);
+        rb.add(&nroots, rsum + n, 1);
         rb.run(s);
+        tmp.free_ptr(rsum);
+        tmp.free_ptr(rat);
     }
     SortBuffers ls{{tmp.alloc<uint64_t>(n, "level keys"), tmp.alloc<uint64_t>(n, "level keys (ping-pong)")},
                    {tmp.alloc<uint32_t>(n, "level vertices"), tmp.alloc<uint32_t>(n, "level vertices (ping-pong)")},
                    0};
-    const int pbits = std::max(1, bits_for(n - 1));
+
+    int dev = 0, cus = 0;
+    TAURUS_HIP(hipGetDevice(&dev));
+    TAURUS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int64_t xgrid = (int64_t)std::max(1, cus) * 8;  // workgroups resident at once
 
     // 4. levels
-    int64_t visited = (int64_t)nf;
+    int64_t visited = nroots;
     while (nf > 0) {
-        fill_i32(reinterpret_cast<int32_t*>(count), 2, 0, s);
-        k_expand<<<(unsigned)ceil_div((int64_t)nf * 64, T), T, 0, s>>>(frontier, (int64_t)nf, sp.list_off,
-                                                                     sp.list_adj, label, pos, claim, listed,
-                                                                     cand, count);
+        fill_i32(reinterpret_cast<int32_t*>(count), 4, 0, s);
+        k_expand<<<(unsigned)std::min<int64_t>(ceil_div(nf, XP_THREADS / 64), xgrid), XP_THREADS, 0, s>>>(
+            frontier, nf, sp.list_off, sp.list_adj, label, pos, claim, pieces, count + 1, cand, count);
         TAURUS_CHECK_LAUNCH();
+        if (sp.list_e > XP_PIECE) {  // else no list is longer than a piece
+            k_expand_pieces<<<(unsigned)xgrid, XP_THREADS, 0, s>>>(frontier, pieces, count + 1, sp.list_off,
+                                                                   sp.list_adj, label, pos, claim, cand, count);
+            TAURUS_CHECK_LAUNCH();
+        }
         unsigned long long nc = 0;
         {
             Readback rb;
@@ -327,7 +456,7 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
         k_level_keys<<<blocks((int64_t)nc), T, 0, s>>>(cand, (int64_t)nc, claim, rank, idbits, ls.keys[0],
                                                        ls.vals[0]);
         TAURUS_CHECK_LAUNCH();
-        radix_sort_u64(ls, (int64_t)nc, pbits + idbits, tmp, s, flag + 1, 1);
+        radix_sort_u64(ls, (int64_t)nc, idbits + std::max(1, bits_for(nf - 1)), tmp, s, flag + 1, 1);
         const uint32_t* sorted = ls.vals[ls.cur];
         k_level_heads<<<blocks((int64_t)nc), T, 0, s>>>(sorted, (int64_t)nc, label, start);
         TAURUS_CHECK_LAUNCH();
@@ -336,7 +465,7 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
         TAURUS_CHECK_LAUNCH();
         k_level_advance<<<blocks((int64_t)nc), T, 0, s>>>(sorted, (int64_t)nc, label, start, next);
         TAURUS_CHECK_LAUNCH();
-        nf = nc;
+        nf = (int64_t)nc;
         visited += (int64_t)nc;
     }
     k_flag<<<blocks(n), T, 0, s>>>(pos, n, flag + 1);
@@ -357,7 +486,7 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
 
 int reorder_impl(const taurus_graph& g, int32_t* new_of_old, hipStream_t s) {
     std::shared_ptr<Csc> csc = build_csc(g, s);  // validates the graph
-    const Search sp{g.row_off, g.col_dst, g.e, csc->in_off, csc->in_src, false, false};
+    const Search sp{g.row_off, g.col_dst, g.e, csc->in_off, csc->in_src, g.e, false, false};
     search_order(g.n, sp, new_of_old, s);
     return TAURUS_OK;
 }
@@ -436,7 +565,7 @@ int reorder_rcm_impl(const taurus_graph& g, int32_t* new_of_old, hipStream_t s) 
     } else {
         fill_i32(reinterpret_cast<int32_t*>(sym_off), 2 * (n + 1), 0, s);
     }
-    const Search sp{sym_off, sym_adj, es, sym_off, sym_adj, true, true};
+    const Search sp{sym_off, sym_adj, es, sym_off, sym_adj, es, true, true};
     search_order(n, sp, new_of_old, s);
     return TAURUS_OK;
 }

@@ -289,3 +289,25 @@ def test_reorder_ta_error_paths(torch_cuda):
     with pytest.raises(T.TaurusError) as ex:
         T.reorder_ta(n, row_off, col_dst, None, 0)
     assert ex.value.status == -1
+
+
+@pytest.mark.parametrize("d", [1023, 1024, 1025, 2048, 5000])
+def test_reorder_list_pieces(torch_cuda, d):
+    """Search lists around the 1,024 entries a level's pieces hold, on two hubs
+    whose in-lists overlap, with isolated vertices and small trees beside the
+    giant one: degree/BFS and RCMK orders equal the oracle's."""
+    import oracle as O
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    _note(f"reorder list pieces d={d}")
+    rng = np.random.default_rng(d)
+    n = 8000
+    u = np.concatenate([np.arange(1, d + 1), np.arange(d // 2, d // 2 + d), rng.integers(0, 6000, 4000),
+                        np.arange(7000, 7500)])
+    v = np.concatenate([np.zeros(d, np.int64), np.full(d, 6500), rng.integers(0, 6000, 4000),
+                        np.arange(7500, 8000)])
+    src, dst = _simple(n, u, v)[:2]
+    g = O.Graph(n, src, dst)
+    row_off, col_dst = T.build_csr(n, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda())
+    assert np.array_equal(T.reorder(n, row_off, col_dst).cpu().numpy(), O.reorder_bfs(g))
+    assert np.array_equal(T.reorder_rcm(n, row_off, col_dst).cpu().numpy(), O.reorder_rcm(g))
