@@ -78,18 +78,18 @@ void gemm_pack_weights_16(const float* W, int K, int Nc, int dtype, std::vector<
                 }
 }
 
-template <int DT, int PANEL_NB>
+template <int DT, int PANEL_NB, int KS>
 __global__ __launch_bounds__(256) void k_gemm_panel(const void* __restrict__ X, int64_t M, int K,
                                                     const typename GemmOp<DT>::frag* __restrict__ Wp, int NBP,
                                                     int Nc, const float* __restrict__ rscale,
                                                     float* __restrict__ Y, int stream, SelfFlush sf) {
-    __shared__ PanelLds<DT, PANEL_NB> lds;
+    __shared__ PanelLds<DT, PANEL_NB, KS> lds;
     // With self messages the column groups start at the first one holding
     // self-half columns: those workgroups wait on accumulator rows, and
     // dispatched first they overlap the purely streaming groups that follow
     // instead of forming the launch's tail.
     const int by = sf.own ? (int)((blockIdx.y + sf.self_col / (PANEL_NB * 16)) % gridDim.y) : (int)blockIdx.y;
-    gemm_panel_block<DT, PANEL_NB>(X, M, K, Wp, NBP, Nc, rscale, Y, blockIdx.x, by, lds, stream != 0, sf);
+    gemm_panel_block<DT, PANEL_NB, KS>(X, M, K, Wp, NBP, Nc, rscale, Y, blockIdx.x, by, lds, stream != 0, sf);
 }
 
 template <int DT>
@@ -101,12 +101,22 @@ static void launch_panel(const void* X, int64_t M, int K, const void* Wp, int Nc
     const SelfFlush f = sf ? *sf : SelfFlush{};
     if (f.own && (rscale || f.self_col + f.d_o > Nc || f.self_col % 4 || f.d_o % 4))
         fail(TAURUS_E_INVALID, "self messages in the transform need unscaled rows and a self half inside Y");
-    if (NBP <= 4) {
-        dim3 grid((unsigned)ceil_div(M, PANEL_ROWS), 1);
-        k_gemm_panel<DT, 4><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);
+    // A chunk whose 128-column groups leave compute units idle takes 64-column
+    // groups with stages of twice the k-blocks: a workgroup there is bound by
+    // the latency of its stages, not by sharing X rows (2,048 x 512 -> 512
+    // fp32, 128 workgroups: 27 us, 256 of them: 17 us; the sums are the
+    // same).
+    int dev = 0, cus = 0;
+    TAURUS_HIP(hipGetDevice(&dev));
+    TAURUS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int64_t panels = ceil_div(M, PANEL_ROWS);
+    const bool narrow = NBP <= 4 || panels * ceil_div(NBP, 8) < cus;
+    if (narrow) {
+        dim3 grid((unsigned)panels, (unsigned)ceil_div(NBP, 4));
+        k_gemm_panel<DT, 4, 2 * PIPE_KS><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);
     } else {
-        dim3 grid((unsigned)ceil_div(M, PANEL_ROWS), (unsigned)ceil_div(NBP, 8));
-        k_gemm_panel<DT, 8><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);
+        dim3 grid((unsigned)panels, (unsigned)ceil_div(NBP, 8));
+        k_gemm_panel<DT, 8, PIPE_KS><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);
     }
     TAURUS_CHECK_LAUNCH();
 }

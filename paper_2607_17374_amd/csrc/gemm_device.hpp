@@ -105,23 +105,23 @@ inline bool transform_streams(int64_t M, int Nc) { return Nc % 32 == 0 && M * (i
 // would be one LDS variable shared by every kernel of the file, which the
 // compiler then addresses less directly).
 constexpr int PIPE_KS = 2;
-template <int DT, int PANEL_NB>
+template <int DT, int PANEL_NB, int KS = PIPE_KS>
 struct PanelLds {
-    static constexpr int SF = PIPE_KS * PANEL_NB * 64;  // fragments per stage
+    static constexpr int SF = KS * PANEL_NB * 64;  // fragments per stage
     typename GemmOp<DT>::frag b[2][SF];
 };
 // The body with the row mapping and the epilogue as parameters: logical row
 // r of the panel reads row arow(r) of X; for each row r < M the epilogue's
 // row(r) returns a per-row writer w, and w(col, value) stores each product
 // of that row, column col < Nc.
-template <int DT, int PANEL_NB, class ARow>
+template <int DT, int PANEL_NB, int KS, class ARow>
 __device__ __attribute__((always_inline)) inline void gemm_panel_compute(const void* __restrict__ X, int64_t M,
                                         int K, const typename GemmOp<DT>::frag* __restrict__ Wp, int NBP, int bx,
-                                        int by, PanelLds<DT, PANEL_NB>& lds, ARow arow,
+                                        int by, PanelLds<DT, PANEL_NB, KS>& lds, ARow arow,
                                         floatx4 (&acc)[PANEL_NB]) {
     typedef GemmOp<DT> Op;
     typedef typename Op::frag frag;
-    constexpr int SF = PanelLds<DT, PANEL_NB>::SF;
+    constexpr int SF = PanelLds<DT, PANEL_NB, KS>::SF;
     constexpr int PER = SF / 256;                // of which each thread stages
     static_assert(SF % 256 == 0, "whole fragments per thread");
     auto& sB = lds.b;
@@ -131,27 +131,27 @@ __device__ __attribute__((always_inline)) inline void gemm_panel_compute(const v
     const int nbs = min(PANEL_NB, NBP - nb0);
     const int64_t row = (int64_t)bx * PANEL_ROWS + wave * 16 + li;
     const int KB = (K + Op::KBLK - 1) / Op::KBLK;
-    const int nst = (KB + PIPE_KS - 1) / PIPE_KS;
+    const int nst = (KB + KS - 1) / KS;
     auto load_w = [&](int st, frag (&r)[PER]) {
 #pragma unroll
         for (int q = 0; q < PER; q++) {
             const int i = q * 256 + tid;
             const int kk = i / (PANEL_NB * 64), rr = i - kk * (PANEL_NB * 64), j = rr >> 6, l = rr & 63;
-            const int kb = st * PIPE_KS + kk;
+            const int kb = st * KS + kk;
             r[q] = (kb < KB && j < nbs) ? Wp[((int64_t)kb * NBP + nb0 + j) * 64 + l] : Op::zero();
         }
     };
-    auto load_a = [&](int st, frag (&a)[PIPE_KS]) {
+    auto load_a = [&](int st, frag (&a)[KS]) {
 #pragma unroll
-        for (int kk = 0; kk < PIPE_KS; kk++) {
-            const int kb = st * PIPE_KS + kk;
+        for (int kk = 0; kk < KS; kk++) {
+            const int kb = st * KS + kk;
             const int k = kb * Op::KBLK + (Op::KBLK / 4) * lk;
             a[kk] = (kb < KB && row < M && k < K) ? Op::load_a(X, arow(row), K, k) : Op::zero();
         }
     };
 #pragma unroll
     for (int j = 0; j < PANEL_NB; j++) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    frag rw[PER], a[PIPE_KS];
+    frag rw[PER], a[KS];
     load_w(0, rw);
     load_a(0, a);
 #pragma unroll
@@ -159,13 +159,13 @@ __device__ __attribute__((always_inline)) inline void gemm_panel_compute(const v
     __syncthreads();
     for (int st = 0; st < nst; st++) {
         const bool more = st + 1 < nst;
-        frag an[PIPE_KS];
+        frag an[KS];
         if (more) {
             load_w(st + 1, rw);
             load_a(st + 1, an);
         }
 #pragma unroll
-        for (int kk = 0; kk < PIPE_KS; kk++) {
+        for (int kk = 0; kk < KS; kk++) {
             frag b[PANEL_NB];
 #pragma unroll
             for (int j = 0; j < PANEL_NB; j++) b[j] = sB[st & 1][(kk * PANEL_NB + j) * 64 + lane];
@@ -176,7 +176,7 @@ __device__ __attribute__((always_inline)) inline void gemm_panel_compute(const v
 #pragma unroll
             for (int q = 0; q < PER; q++) sB[(st + 1) & 1][q * 256 + tid] = rw[q];
 #pragma unroll
-            for (int kk = 0; kk < PIPE_KS; kk++) a[kk] = an[kk];
+            for (int kk = 0; kk < KS; kk++) a[kk] = an[kk];
         }
         __syncthreads();
     }
@@ -190,7 +190,7 @@ __device__ __attribute__((always_inline)) inline void gemm_panel_core(const void
                                         const typename GemmOp<DT>::frag* __restrict__ Wp, int NBP, int Nc, int bx,
                                         int by, PanelLds<DT, PANEL_NB>& lds, ARow arow, Epi epi) {
     floatx4 acc[PANEL_NB];
-    gemm_panel_compute<DT, PANEL_NB>(X, M, K, Wp, NBP, bx, by, lds, arow, acc);
+    gemm_panel_compute<DT, PANEL_NB, PIPE_KS>(X, M, K, Wp, NBP, bx, by, lds, arow, acc);
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
     const int nb0 = by * PANEL_NB, nbs = min(PANEL_NB, NBP - nb0);
     const int64_t rbase = (int64_t)bx * PANEL_ROWS + (threadIdx.x >> 6) * 16 + 4 * lk;
@@ -251,9 +251,9 @@ struct SelfRows {
 // stores, for a Y too large to stay in L2 until its scatter reads it.
 // Ends with the tile read: a caller that writes the buffers again first
 // passes a barrier.
-template <int DT, int PANEL_NB>
+template <int DT, int PANEL_NB, int KS>
 __device__ __attribute__((always_inline)) inline void store_panel_staged(const floatx4 (&acc)[PANEL_NB],
-                                        PanelLds<DT, PANEL_NB>& lds, int64_t M, int Nc,
+                                        PanelLds<DT, PANEL_NB, KS>& lds, int64_t M, int Nc,
                                         const float* __restrict__ rscale, float* __restrict__ Y, int bx, int by,
                                         bool stream, const SelfFlush& sf, const SelfRows& sr) {
     constexpr int TW = PANEL_NB * 16;  // tile width (fp32 columns)
@@ -338,11 +338,11 @@ __device__ __attribute__((always_inline)) inline void store_panel_staged(const f
 // Y = X W, rows [64 bx, 64 bx + 64) and column blocks [PANEL_NB by,
 // PANEL_NB by + PANEL_NB), through the staged store (with the self
 // messages sf takes).
-template <int DT, int PANEL_NB>
+template <int DT, int PANEL_NB, int KS = PIPE_KS>
 __device__ __attribute__((always_inline)) inline void gemm_panel_block(const void* __restrict__ X, int64_t M, int K,
                                         const typename GemmOp<DT>::frag* __restrict__ Wp, int NBP, int Nc,
                                         const float* __restrict__ rscale, float* __restrict__ Y, int bx, int by,
-                                        PanelLds<DT, PANEL_NB>& lds, bool stream, const SelfFlush& sf) {
+                                        PanelLds<DT, PANEL_NB, KS>& lds, bool stream, const SelfFlush& sf) {
     // a group with self messages: lane l of every wave reads row l's flag
     // and counts, and the wave turns them into SelfRows (uniform, so they
     // hold no vector registers through the products); the epilogue then
@@ -361,9 +361,9 @@ __device__ __attribute__((always_inline)) inline void gemm_panel_block(const voi
         sr.last = __ballot(pe.x == 1);
     }
     floatx4 acc[PANEL_NB];
-    gemm_panel_compute<DT, PANEL_NB>(X, M, K, Wp, NBP, bx, by, lds, [](int64_t r) { return r; }, acc);
+    gemm_panel_compute<DT, PANEL_NB, KS>(X, M, K, Wp, NBP, bx, by, lds, [](int64_t r) { return r; }, acc);
     // every wave is past the last stage's barrier: the buffers are free
-    store_panel_staged<DT, PANEL_NB>(acc, lds, M, Nc, rscale, Y, bx, by, stream, sf, sr);
+    store_panel_staged<DT, PANEL_NB, KS>(acc, lds, M, Nc, rscale, Y, bx, by, stream, sf, sr);
 }
 
 }  // namespace taurus
