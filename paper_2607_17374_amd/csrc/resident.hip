@@ -148,23 +148,198 @@ __global__ void k_res_victims(int64_t n, int32_t k, int32_t tau, int64_t tie_tak
     if (add) victims[at] = (int32_t)v;
 }
 
-// one wave per victim: row to the host store, slot back to the free list
+// ---- eviction decided on the device ----
+// The same choice without reading anything back: the host queues every step
+// for a chunk that may need evictions, and the steps find out from device
+// memory (ResPlan) whether and how many.  Used while the threshold bin holds
+// one key value for certain and the vertices are few enough for
+// each wave to add up the tie counts before its own.
+
+// this chunk's eviction, written by k_res_threshold
+struct ResPlan {
+    int64_t victims;    // M: rows to evict, 0 = none
+    int64_t tie_take;   // of the threshold bin, by lowest ID
+    int32_t tau;        // threshold bin
+    int32_t bad;        // set once a chunk's rows could not be freed
+};
+
+// rows this chunk is short of, from the listed count and the free-list top
+__device__ inline int64_t res_short(const unsigned long long* listed, const int32_t* top) {
+    return (int64_t)*listed - (int64_t)*top;
+}
+
+__global__ __launch_bounds__(1024) void k_res_hist_dev(int64_t n, int32_t k, const int32_t* __restrict__ slot_of,
+                                                       const uint8_t* __restrict__ hub, EvictKeys e,
+                                                       const unsigned long long* __restrict__ listed,
+                                                       const int32_t* __restrict__ top,
+                                                       unsigned int* __restrict__ hist) {
+    __shared__ unsigned int h[RES_BINS];
+    if (res_short(listed, top) <= 0) return;  // uniform over the grid
+    for (int i = threadIdx.x; i < RES_BINS; i += blockDim.x) h[i] = 0;
+    __syncthreads();
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+        if (res_candidate((int)v, k, slot_of, hub, e.dc_mark, e.cnt)) atomicAdd(&h[res_key((int)v, k, e)], 1u);
+    __syncthreads();
+    for (int i = threadIdx.x; i < RES_BINS; i += blockDim.x)
+        if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+// One workgroup: the first bin at which the running count reaches the rows
+// the chunk is short of.  Leaves the histogram zeroed for the next chunk.
+__global__ __launch_bounds__(1024) void k_res_threshold(const unsigned long long* __restrict__ listed,
+                                                        const int32_t* __restrict__ top,
+                                                        unsigned int* __restrict__ hist, ResPlan* __restrict__ plan) {
+    constexpr int PER = RES_BINS / 1024;
+    __shared__ int64_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t need = res_short(listed, top);
+    if (need <= 0) {  // uniform
+        if (tid == 0) plan->victims = 0;
+        return;
+    }
+    unsigned int h[PER];
+    int64_t own = 0;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        h[i] = hist[tid * PER + i];
+        hist[tid * PER + i] = 0;
+        own += h[i];
+    }
+    int64_t incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int64_t run = incl - own, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; w++) {
+        if (w < wave) run += wsum[w];
+        all += wsum[w];
+    }
+    if (all < need) {  // the pool holds a chunk's rows, so this cannot be: nothing is evicted
+        if (tid == 0) {
+            plan->victims = 0;
+            plan->bad = 1;
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        if (run < need && run + (int64_t)h[i] >= need) {
+            plan->victims = need;
+            plan->tie_take = need - run;
+            plan->tau = tid * PER + i;
+        }
+        run += h[i];
+    }
+}
+
+// Vertices by the wave: 256 consecutive ones, 64 a round (1,024 left most
+// compute units idle at 262K vertices: 12.8 us for the tie counts, 5.6 us
+// this way).
+constexpr int RES_WTILE = 256;
+__global__ __launch_bounds__(256) void k_res_tie_counts(int64_t n, int32_t k, const int32_t* __restrict__ slot_of,
+                                                        const uint8_t* __restrict__ hub, EvictKeys e,
+                                                        const ResPlan* __restrict__ plan,
+                                                        int32_t* __restrict__ ties) {
+    if (plan->victims == 0) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (w * RES_WTILE >= n) return;
+    const int32_t tau = plan->tau;
+    int c = 0;
+    for (int r = 0; r < RES_WTILE; r += 64) {
+        const int64_t v = w * RES_WTILE + r + lane;
+        const bool tie = v < n && res_candidate((int)v, k, slot_of, hub, e.dc_mark, e.cnt) && res_key((int)v, k, e) == tau;
+        c += (int)__popcll(__ballot(tie));
+    }
+    if (lane == 0) ties[w] = c;
+}
+
+__global__ __launch_bounds__(256) void k_res_victims_dev(int64_t n, int32_t k, const int32_t* __restrict__ slot_of,
+                                                         const uint8_t* __restrict__ hub, EvictKeys e,
+                                                         const ResPlan* __restrict__ plan,
+                                                         const int32_t* __restrict__ ties,
+                                                         int32_t* __restrict__ victims,
+                                                         unsigned long long* __restrict__ count) {
+    if (plan->victims == 0) return;
+    const int lane = threadIdx.x & 63;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    if (w * RES_WTILE >= n) return;
+    const int32_t tau = plan->tau;
+    int64_t before = 0;  // ties before this wave's vertices
+    for (int64_t i = lane; i < w; i += 64) before += ties[i];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+    const int64_t take = plan->tie_take;
+    constexpr int R = RES_WTILE / 64;
+    uint64_t add[R];
+    int total = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int64_t v = w * RES_WTILE + r * 64 + lane;
+        bool below = false, tie = false;
+        if (v < n && res_candidate((int)v, k, slot_of, hub, e.dc_mark, e.cnt)) {
+            const int b = res_key((int)v, k, e);
+            below = b < tau;
+            tie = b == tau;
+        }
+        const uint64_t tb = __ballot(tie);
+        add[r] = __ballot(below || (tie && before + (int64_t)__popcll(tb & lt) < take));
+        before += __popcll(tb);
+        total += (int)__popcll(add[r]);
+    }
+    if (total == 0) return;
+    unsigned long long at = 0;
+    if (lane == 0) at = atomicAdd(count, (unsigned long long)total);
+    at = __shfl(at, 0);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        if ((add[r] >> lane) & 1) victims[at + __popcll(add[r] & lt)] = (int32_t)(w * RES_WTILE + r * 64 + lane);
+        at += __popcll(add[r]);
+    }
+}
+
+// after the assignment: the free-list top, the evictions made, and the
+// counters of the next chunk
+__global__ void k_res_settle(int32_t* __restrict__ top, unsigned long long* __restrict__ listed,
+                             unsigned long long* __restrict__ chosen, ResPlan* __restrict__ plan,
+                             unsigned long long* __restrict__ evictions) {
+    *top += (int32_t)plan->victims - (int32_t)*listed;
+    if ((int64_t)*chosen != plan->victims) plan->bad = 1;
+    *evictions += (unsigned long long)plan->victims;
+    *listed = 0;
+    *chosen = 0;
+}
+
+// one wave per victim (waves stride over them): row to the host store, slot
+// back to the free list at base + j (plan: count and base from the device)
 __global__ __launch_bounds__(256) void k_res_evict(const int32_t* __restrict__ victims, int64_t nv, int d_o,
                                                    float* __restrict__ pool, float* __restrict__ store,
                                                    int32_t* __restrict__ slot_of, uint8_t* __restrict__ evicted,
-                                                   int32_t* __restrict__ free_list, int32_t base) {
-    const int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+                                                   int32_t* __restrict__ free_list, int32_t base,
+                                                   const ResPlan* __restrict__ plan, const int32_t* __restrict__ top) {
     const int lane = threadIdx.x & 63;
-    if (j >= nv) return;
-    const int v = victims[j];
-    const int32_t s = slot_of[v];
-    const float4* src = reinterpret_cast<const float4*>(pool + (int64_t)s * d_o);
-    float4* dst = reinterpret_cast<float4*>(store + (int64_t)v * d_o);
-    for (int q = lane; q < d_o / 4; q += 64) dst[q] = src[q];
-    if (lane == 0) {
-        slot_of[v] = -1;
-        evicted[v] = 1;
-        free_list[base + j] = s;
+    if (plan) {
+        nv = plan->victims;
+        base = *top;
+    }
+    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; j < nv; j += nw) {  // uniform
+        const int v = victims[j];
+        const int32_t s = slot_of[v];
+        const float4* src = reinterpret_cast<const float4*>(pool + (int64_t)s * d_o);
+        float4* dst = reinterpret_cast<float4*>(store + (int64_t)v * d_o);
+        for (int q = lane; q < d_o / 4; q += 64) dst[q] = src[q];
+        if (lane == 0) {
+            slot_of[v] = -1;
+            evicted[v] = 1;
+            free_list[base + j] = s;
+        }
     }
 }
 
@@ -178,7 +353,8 @@ __global__ __launch_bounds__(256) void k_res_evict(const int32_t* __restrict__ v
 __global__ __launch_bounds__(256) void k_res_assign(const int32_t* __restrict__ need, int64_t nn,
                                                     const unsigned long long* __restrict__ nn_dev, int d_o,
                                                     const int32_t* __restrict__ free_list, int64_t top,
-                                                    const int32_t* __restrict__ top_dev, int32_t k,
+                                                    const int32_t* __restrict__ top_dev,
+                                                    const ResPlan* __restrict__ plan, int32_t k,
                                                     float* __restrict__ pool, const float* __restrict__ store,
                                                     int32_t* __restrict__ slot_of, uint8_t* __restrict__ evicted,
                                                     int32_t* __restrict__ want, int32_t* __restrict__ adm,
@@ -188,11 +364,14 @@ __global__ __launch_bounds__(256) void k_res_assign(const int32_t* __restrict__ 
     if (nn_dev) {
         nn = (int64_t)*nn_dev;
         top = *top_dev;
+        if (plan) top += plan->victims;
     }
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; j < nn; j += nw) {  // uniform
         const int v = need[j];
-        const int32_t s = free_list[top - 1 - j];
+        // j < top: the pool holds a chunk's rows (else plan->bad is set and the
+        // layer fails; row 0 keeps its writes inside the pool until then)
+        const int32_t s = j < top ? free_list[top - 1 - j] : 0;
         if (evicted[v]) {
             const float4* src = reinterpret_cast<const float4*>(store + (int64_t)v * d_o);
             float4* dst = reinterpret_cast<float4*>(pool + (int64_t)s * d_o);
@@ -263,6 +442,17 @@ __global__ void k_sum_hub_messages(const int32_t* __restrict__ m, const uint8_t*
     if (v < n && hub[v]) atomicAdd(sum, (unsigned long long)m[v]);
 }
 
+// *mx = the largest message count of a vertex that is no hub (hubs are never evicted)
+__global__ __launch_bounds__(256) void k_max_count(const int32_t* __restrict__ m, const uint8_t* __restrict__ hub,
+                                                   int64_t n, unsigned long long* __restrict__ mx) {
+    int x = 0;
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256)
+        if (!hub[v]) x = max(x, m[v]);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
+    if ((threadIdx.x & 63) == 0 && x > 0) atomicMax(mx, (unsigned long long)x);
+}
+
 // histogram of per-vertex reload counts; the last bin takes the rest
 __global__ void k_reload_hist(const int32_t* __restrict__ reloads_of, int64_t n, int bins,
                               unsigned long long* __restrict__ hist) {
@@ -296,7 +486,9 @@ Residency::Residency(hipStream_t s, int64_t n_, int d_o_, int64_t slots, int64_t
     hub = arena.alloc<uint8_t>(n, "hub flags");
     evicted = arena.alloc<uint8_t>(n, "evicted flags");
     hist = arena.alloc<unsigned int>(RES_BINS, "pending histogram");
-    counters = arena.alloc<unsigned long long>(4, "residency counters");
+    counters = arena.alloc<unsigned long long>(8 + sizeof(ResPlan) / 8, "residency counters and eviction plan");
+    static_assert(sizeof(ResPlan) % 8 == 0, "the plan follows the counters");
+    plan_dev = counters + 8;
     free_list = arena.alloc<int32_t>(S, "free slots");
     free_top = arena.alloc<int32_t>(1, "free slot count");
     pool = arena.alloc<float>(S * (int64_t)d_o, "accumulator pool");
@@ -309,7 +501,8 @@ Residency::Residency(hipStream_t s, int64_t n_, int d_o_, int64_t slots, int64_t
     TAURUS_CHECK_LAUNCH();
     k_fill_u8<<<nb, T, 0, s>>>(evicted, n, 0);
     TAURUS_CHECK_LAUNCH();
-    fill_i32(reinterpret_cast<int32_t*>(counters), 8, 0, s);
+    fill_i32(reinterpret_cast<int32_t*>(counters), 16 + sizeof(ResPlan) / 4, 0, s);
+    fill_i32(reinterpret_cast<int32_t*>(hist), RES_BINS, 0, s);
     // hubs: the first H vertices by (message count descending, ID ascending)
     Arena tmp(s);
     uint32_t* order = nullptr;
@@ -337,9 +530,19 @@ Residency::Residency(hipStream_t s, int64_t n_, int d_o_, int64_t slots, int64_t
         k_sum_hub_messages<<<nb, T, 0, s>>>(m, hub, n, counters + 3);
         TAURUS_CHECK_LAUNCH();
     }
+    k_max_count<<<std::min<unsigned>(nb, 512), T, 0, s>>>(m, hub, n, counters + 5);
+    TAURUS_CHECK_LAUNCH();
+    unsigned long long max_m = 0;
     Readback rb;
     rb.add(&hub_msgs, counters + 3, 1);
+    rb.add(&max_m, counters + 5, 1);
     rb.run(s);
+    // eviction on the device: every candidate's bin holds one key value (a
+    // pending count is at most |M(v)| + 1; the last pending bin would hold several), and
+    // a wave adds up at most 16,384 tie counts
+    const bool one_key = policy == TAURUS_EVICT_RANDOM ||
+                         (policy == TAURUS_EVICT_PENDING ? (int64_t)max_m + 1 < RES_BINS - 1 : chunk_shift == 0);
+    on_device = one_key && ceil_div(n, RES_WTILE) <= 16384;
     hub_share = messages > 0 ? (double)hub_msgs / (double)messages : 0.0;
     // host store for evicted rows: pinned, written and read by kernels only
     store_host = static_cast<float*>(pinned_acquire((size_t)n * d_o * sizeof(float), &store_cap));
@@ -355,7 +558,8 @@ void Residency::prepare(const ResChunk& c, int32_t k, const int2* cnt, hipStream
     const int T = 256;
     const int64_t total = c.total();
     unsigned long long* need_count = counters;
-    fill_i32(reinterpret_cast<int32_t*>(need_count), 2, 0, s);
+    if (!counters_clear) fill_i32(reinterpret_cast<int32_t*>(need_count), 2, 0, s);
+    counters_clear = false;
     k_res_collect<<<(unsigned)ceil_div(std::max<int64_t>(total, 1), T), T, 0, s>>>(c, total, k, slot_of, cnt, dc_mark,
                                                                                   want, need, need_count);
     TAURUS_CHECK_LAUNCH();
@@ -365,13 +569,43 @@ void Residency::prepare(const ResChunk& c, int32_t k, const int2* cnt, hipStream
     if (total <= free_lb) {
         if (total > 0) {
             k_res_assign<<<(unsigned)std::min<int64_t>(ceil_div(total, 4), grid_cap), T, 0, s>>>(
-                need, 0, need_count, d_o, free_list, 0, free_top, k, pool, store_dev, slot_of, evicted, want, adm,
-                reloads_of, counters + 2);
+                need, 0, need_count, d_o, free_list, 0, free_top, nullptr, k, pool, store_dev, slot_of, evicted, want,
+                adm, reloads_of, counters + 2);
             TAURUS_CHECK_LAUNCH();
             k_res_take<<<1, 1, 0, s>>>(free_top, need_count);
             TAURUS_CHECK_LAUNCH();
         }
         free_lb -= total;
+        return;
+    }
+    if (on_device) {
+        // three readbacks a chunk cost more than the steps themselves (262K
+        // vertices in 2,048-vertex chunks, half of them evicting: 24.6 ms a
+        // layer with them, 20.6 ms without)
+        const EvictKeys ek{policy, chunk_shift, seed, cnt, dc_mark, adm};
+        ResPlan* plan = static_cast<ResPlan*>(plan_dev);
+        unsigned long long* chosen = counters + 1;
+        const unsigned wblocks = (unsigned)ceil_div(ceil_div(n, RES_WTILE), 4);
+        const unsigned hblocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 4096), 1024));
+        k_res_hist_dev<<<hblocks, 1024, 0, s>>>(n, k, slot_of, hub, ek, need_count, free_top, hist);
+        TAURUS_CHECK_LAUNCH();
+        k_res_threshold<<<1, 1024, 0, s>>>(need_count, free_top, hist, plan);
+        TAURUS_CHECK_LAUNCH();
+        k_res_tie_counts<<<wblocks, T, 0, s>>>(n, k, slot_of, hub, ek, plan, tie);
+        TAURUS_CHECK_LAUNCH();
+        k_res_victims_dev<<<wblocks, T, 0, s>>>(n, k, slot_of, hub, ek, plan, tie, victims, chosen);
+        TAURUS_CHECK_LAUNCH();
+        const unsigned rows = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(total, 4), 1024));
+        k_res_evict<<<rows, T, 0, s>>>(victims, 0, d_o, pool, store_dev, slot_of, evicted, free_list, 0, plan,
+                                       free_top);
+        TAURUS_CHECK_LAUNCH();
+        k_res_assign<<<rows, T, 0, s>>>(need, 0, need_count, d_o, free_list, 0, free_top, plan, k, pool, store_dev,
+                                        slot_of, evicted, want, adm, reloads_of, counters + 2);
+        TAURUS_CHECK_LAUNCH();
+        k_res_settle<<<1, 1, 0, s>>>(free_top, need_count, chosen, plan, counters + 4);
+        TAURUS_CHECK_LAUNCH();
+        counters_clear = true;
+        free_lb = 0;
         return;
     }
     unsigned long long nn = 0;
@@ -445,15 +679,15 @@ void Residency::prepare(const ResChunk& c, int32_t k, const int2* cnt, hipStream
         if ((int64_t)got != M)
             fail(TAURUS_E_DEVICE, "eviction chose %llu victims instead of %lld", got, (long long)M);
         k_res_evict<<<(unsigned)ceil_div(M * 64, T), T, 0, s>>>(victims, M, d_o, pool, store_dev, slot_of, evicted,
-                                                              free_list, top);
+                                                              free_list, top, nullptr, nullptr);
         TAURUS_CHECK_LAUNCH();
-        evictions += M;
+        host_evictions += M;
         top += (int32_t)M;
     }
     if (nn > 0) {
         k_res_assign<<<(unsigned)std::min<int64_t>(ceil_div((int64_t)nn, 4), grid_cap), T, 0, s>>>(
-            need, (int64_t)nn, nullptr, d_o, free_list, top, nullptr, k, pool, store_dev, slot_of, evicted, want,
-            adm, reloads_of, counters + 2);
+            need, (int64_t)nn, nullptr, d_o, free_list, top, nullptr, nullptr, k, pool, store_dev, slot_of, evicted,
+            want, adm, reloads_of, counters + 2);
         TAURUS_CHECK_LAUNCH();
         k_res_set<<<1, 1, 0, s>>>(free_top, top - (int32_t)nn);
         TAURUS_CHECK_LAUNCH();
@@ -482,10 +716,15 @@ void Residency::reload_histogram(int64_t* counts, int bins, hipStream_t s) {
 }
 
 int64_t Residency::reload_count(hipStream_t s) {
-    unsigned long long r = 0;
+    unsigned long long r = 0, ev = 0;
+    ResPlan p{};
     Readback rb;
     rb.add(&r, counters + 2, 1);
+    rb.add(&ev, counters + 4, 1);
+    rb.add(&p, static_cast<ResPlan*>(plan_dev), 1);
     rb.run(s);
+    if (p.bad) fail(TAURUS_E_BUDGET, "accumulator pool: a chunk needed more slots than could be freed");
+    evictions = host_evictions + (int64_t)ev;
     return (int64_t)r;
 }
 

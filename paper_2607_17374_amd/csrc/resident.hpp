@@ -38,6 +38,8 @@ public:
     void prepare(const ResChunk& c, int32_t k, const int2* cnt, hipStream_t s);
     // free the slots of the chunk's destinations that completed
     void release(const ResChunk& c, const int2* cnt, hipStream_t s);
+    // reloads so far; brings `evictions` up to date and fails if a chunk's
+    // rows could not be freed
     int64_t reload_count(hipStream_t s);
     // counts[i] = vertices reloaded i times (i < bins - 1), counts[bins - 1] = the rest
     void reload_histogram(int64_t* counts, int bins, hipStream_t s);
@@ -58,7 +60,8 @@ private:
     int64_t* tie_rank = nullptr;
     uint8_t *hub = nullptr, *evicted = nullptr;
     unsigned int* hist = nullptr;
-    unsigned long long* counters = nullptr;  // [0] listed, [1] victims, [2] reloads, [3] hub messages
+    unsigned long long* counters = nullptr;  // [0] listed, [1] victims, [2] reloads, [3] hub messages, [4] evictions
+                                             // decided on the device, [5] largest message count
     int32_t *free_list = nullptr, *free_top = nullptr;
     float* store_host = nullptr;  // pinned [n][d_o] (from the pinned block cache)
     size_t store_cap = 0;
@@ -68,6 +71,10 @@ private:
     // are assigned without reading anything back (releases only raise the
     // true count)
     int64_t free_lb = 0;
+    bool on_device = false;        // evictions are decided by kernels (k_res_threshold)
+    bool counters_clear = false;   // the listed count is already zero
+    int64_t host_evictions = 0;    // decided on the host
+    void* plan_dev = nullptr;      // ResPlan
 };
 
 }  // namespace taurus
