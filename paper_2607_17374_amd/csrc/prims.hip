@@ -315,11 +315,42 @@ void Readback::add_bytes(void* host, const void* dev, size_t bytes) {
     total_ += (bytes + 15) & ~(size_t)15;
 }
 
+// A few small reads leave in one kernel that writes them to the mapped
+// staging buffer: a copy command each (the chunk index reads eight list
+// positions at once) costs several microseconds of host and of queue time.
+constexpr int READ_ITEMS = 16;
+constexpr size_t READ_BYTES = 32 << 10;  // more than this a copy engine moves faster
+struct ReadItems {
+    const uint32_t* src[READ_ITEMS];
+    uint32_t words[READ_ITEMS], at[READ_ITEMS];  // at: staging word
+    int n;
+};
+__global__ __launch_bounds__(256) void k_read_back(ReadItems r, uint32_t* __restrict__ stage) {
+    for (int i = 0; i < r.n; i++)
+        for (uint32_t w = threadIdx.x; w < r.words[i]; w += 256) stage[r.at[i] + w] = r.src[i][w];
+}
+
 void Readback::run(hipStream_t s) {
     if (items_.empty()) return;
     char* stage = static_cast<char*>(pinned_staging(total_));
-    for (const Item& it : items_)
-        TAURUS_HIP(hipMemcpyAsync(stage + it.off, it.dev, it.bytes, hipMemcpyDeviceToHost, s));
+    ReadItems r{};
+    bool small = items_.size() <= (size_t)READ_ITEMS && total_ <= READ_BYTES;
+    for (const Item& it : items_) {
+        if (!small) break;
+        small = it.bytes % 4 == 0 && reinterpret_cast<uintptr_t>(it.dev) % 4 == 0;
+        r.src[r.n] = static_cast<const uint32_t*>(it.dev);
+        r.words[r.n] = (uint32_t)(it.bytes / 4);
+        r.at[r.n++] = (uint32_t)(it.off / 4);
+    }
+    if (small) {
+        void* dev = nullptr;
+        TAURUS_HIP(hipHostGetDevicePointer(&dev, stage, 0));
+        k_read_back<<<1, 256, 0, s>>>(r, static_cast<uint32_t*>(dev));
+        TAURUS_CHECK_LAUNCH();
+    } else {
+        for (const Item& it : items_)
+            TAURUS_HIP(hipMemcpyAsync(stage + it.off, it.dev, it.bytes, hipMemcpyDeviceToHost, s));
+    }
     TAURUS_HIP(hipStreamSynchronize(s));
     for (const Item& it : items_) std::memcpy(it.host, stage + it.off, it.bytes);
     items_.clear();
