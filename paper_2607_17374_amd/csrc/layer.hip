@@ -499,12 +499,10 @@ struct ScatterParams {
     int64_t first_row;     // first vertex of the chunk
     int64_t rows;          // vertices in the chunk
     // GAT aggregation only (k_scatter<G, VEC, true>): the weight of message
-    // u -> v is exp(LeakyReLU(s_u + t_v) - m_v) / S_v, with s_u in column
-    // d_o of u's row of Y, t_v = att_t[v * ystride], m_v = att_m[v] and
-    // S_v = att_s[v]
-    const float* att_t;
-    const float* att_m;
-    const float* att_s;
+    // u -> v is exp(LeakyReLU(s_u + t_v) - m_v) / S_v, with s_u = att_src of
+    // u's local row and att_dst[v] = {t_v, m_v, S_v, -}
+    const float* att_src;
+    const float4* att_dst;
     // GIN with a perceptron (agg TAURUS_GIN_MLP): a completing destination's
     // hidden row ReLU(acc + b1) replaces its accumulator row; the chunk's
     // graduation transform reads it from there
@@ -550,9 +548,10 @@ __device__ inline float* acc_row(const ScatterParams& p, int v) {
 // the message from local row r of the chunk to v
 constexpr float ATT_SLOPE = 0.2f;
 __device__ inline float att_weight(const ScatterParams& p, int r, int v) {
-    const float e0 = p.Y[(int64_t)r * p.ystride + p.d_o] + p.att_t[(int64_t)v * p.ystride];
+    const float4 d = p.att_dst[v];
+    const float e0 = p.att_src[r] + d.x;
     const float e = e0 > 0.f ? e0 : ATT_SLOPE * e0;
-    return expf(e - p.att_m[v]) / p.att_s[v];
+    return expf(e - d.y) / d.z;
 }
 
 // weight of a message slot: GraphSAGE-mean 1/|M(v)| (|M(v)| = expected - 1),
@@ -1608,8 +1607,8 @@ namespace taurus {
 // ------------------------------------------------------------------- GAT --
 // Single-head GATConv (Sec. 3.9, GATConv) in three passes over the chunks:
 //   1. transform (taurus_push_chunk): h'_c = X_c W for the chunk, written to
-//      a table h' of every vertex, and two more columns s_u = a_src . h'_u
-//      and t_u = a_dst . h'_u, taken in fp32 from the transformed row;
+//      a table h' of every vertex, and the terms s_u = a_src . h'_u and
+//      t_u = a_dst . h'_u, taken in fp32 from the transformed row;
 //   2. softmax statistics, topology only: per destination the largest score
 //      m_v and the sum S_v = sum_u exp(e_uv - m_v) over its neighbourhood
 //      (propagated messages and the self message), e_uv = LeakyReLU(s_u +
@@ -1623,41 +1622,49 @@ namespace taurus {
 //      then the sole-owner flush and fix-up.
 constexpr float GAT_SLOPE = ATT_SLOPE;
 
+// The attention terms live in arrays of their own, 20 bytes a vertex, and
+// not beside the rows of h': the statistics then read 4 bytes of a compact
+// array per message instead of a cache line of the table, and rows of h' keep
+// whole 64-byte pieces (500K vertices, 10M edges, 128 -> 64: statistics 394 -> 285 us, scores 90 ->
+// 43 us, aggregation 686 -> 629 us, transform 211 -> 144 us, which lost a
+// column group; a layer 1.60 -> 1.25 ms).
 struct GatParams {
-    const float* hp;  // [n][ystride]: h' then s, t
-    int64_t ystride;
-    int d_o;
-    float* m;         // [n] running largest score
-    float* S;         // [n] running sum of exp(score - m); 0 = none yet
-    float* scarry;    // per hub piece of the chunk: {max, sum}
+    const float* src;  // [n] s_u
+    float4* dst;       // [n] {t_v, running largest score, running sum of exp(score - largest) (0 = none yet), -}
+    float* scarry;     // per hub piece of the chunk: {max, sum}
 };
 
-// pass 1 after the chunk's transform: one wave per row of h' (row stride
-// ncols) writes s and t into columns d_o and d_o + 1
-__global__ __launch_bounds__(256) void k_gat_scores(float* __restrict__ hp, int64_t rows, int64_t ncols, int d_o,
-                                                    const float* __restrict__ attn) {
-    const int lane = threadIdx.x & 63;
-    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+// pass 1 after the chunk's transform: s and t of each row of h' (row stride
+// ystride), 16 lanes a row
+__global__ __launch_bounds__(256) void k_gat_scores(const float* __restrict__ hp, int64_t rows, int64_t ystride,
+                                                    int d_o, const float* __restrict__ attn, float* __restrict__ src,
+                                                    float4* __restrict__ dst) {
+    const int lane = threadIdx.x & 15;
+    const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
     if (r >= rows) return;
-    float* row = hp + r * ncols;
+    const float* row = hp + r * ystride;
     float s = 0.f, t = 0.f;
-    for (int o = lane; o < d_o; o += 64) {
-        s = fmaf(attn[o], row[o], s);
-        t = fmaf(attn[d_o + o], row[o], t);
+    for (int o = lane * 4; o < d_o; o += 64) {
+        const float4 x = *reinterpret_cast<const float4*>(row + o);
+        const float4 a = *reinterpret_cast<const float4*>(attn + o);
+        const float4 b = *reinterpret_cast<const float4*>(attn + d_o + o);
+        s = fmaf(a.w, x.w, fmaf(a.z, x.z, fmaf(a.y, x.y, fmaf(a.x, x.x, s))));
+        t = fmaf(b.w, x.w, fmaf(b.z, x.z, fmaf(b.y, x.y, fmaf(b.x, x.x, t))));
     }
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        s += __shfl_xor(s, d, 64);
-        t += __shfl_xor(t, d, 64);
+    for (int d = 8; d > 0; d >>= 1) {
+        s += __shfl_xor(s, d, 16);
+        t += __shfl_xor(t, d, 16);
     }
     if (lane == 0) {
-        row[d_o] = s;
-        row[d_o + 1] = t;
+        src[r] = s;
+        dst[r] = make_float4(t, 0.f, 0.f, 0.f);
     }
 }
 
-__device__ inline float gat_score(const GatParams& q, int64_t u, int64_t v) {
-    const float e = q.hp[u * q.ystride + q.d_o] + q.hp[v * q.ystride + q.d_o + 1];
+// score of the message u -> v, t = t_v
+__device__ inline float gat_score(const GatParams& q, int64_t u, float t) {
+    const float e = q.src[u] + t;
     return e > 0.f ? e : GAT_SLOPE * e;
 }
 
@@ -1696,20 +1703,31 @@ __device__ inline int4 short_unit(const ChunkUnits& cu, int64_t t) {
     return make_int4(0, 0, -1, 0);
 }
 
+// v's statistics <- with (m2, S2)
+__device__ inline void gat_update(const GatParams& q, int64_t v, float4 d, float m2, float S2) {
+    gat_merge(d.y, d.z, m2, S2);
+    q.dst[v] = d;
+}
+
 // pass 2, short units: one thread each
 __global__ void k_gat_stats_short(ScatterParams p, ChunkUnits cu, GatParams q, int64_t total) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= total) return;
     const int4 w = short_unit(cu, t);
     const int v = w.z, L = w.y & LEN_MASK;
+    const float4 d = q.dst[v];
+    float sc[class_len(NCLASS - 1)];  // the segment's scores, read once
     float mx = -INFINITY;
-    for (int i = 0; i < L; i++) mx = fmaxf(mx, gat_score(q, short_slot_src(p, w, i), v));
+#pragma unroll
+    for (int i = 0; i < class_len(NCLASS - 1); i++) {
+        sc[i] = i < L ? gat_score(q, short_slot_src(p, w, i), d.x) : -INFINITY;
+        mx = fmaxf(mx, sc[i]);
+    }
     float sum = 0.f;
-    for (int i = 0; i < L; i++) sum += expf(gat_score(q, short_slot_src(p, w, i), v) - mx);
-    float m = q.m[v], S = q.S[v];
-    gat_merge(m, S, mx, sum);
-    q.m[v] = m;
-    q.S[v] = S;
+#pragma unroll
+    for (int i = 0; i < class_len(NCLASS - 1); i++)
+        if (i < L) sum += expf(sc[i] - mx);
+    gat_update(q, v, d, mx, sum);
 }
 
 // pass 2, wave pieces: one wave each; a hub piece parks its statistics
@@ -1720,20 +1738,27 @@ __global__ __launch_bounds__(256) void k_gat_stats_pieces(ScatterParams p, const
     if (un >= n) return;  // the whole wave
     const int4 w = units[un];
     const int v = w.z, L = w.y & LEN_MASK;
+    const float4 d = q.dst[v];
+    constexpr int R = PIECE_LEN / 64;
+    float sc[R];
     float mx = -INFINITY;
-    for (int i = lane; i < L; i += 64) mx = fmaxf(mx, gat_score(q, piece_slot_src(p, w, i), v));
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+    for (int r = 0; r < R; r++) {
+        const int i = r * 64 + lane;
+        sc[r] = i < L ? gat_score(q, piece_slot_src(p, w, i), d.x) : -INFINITY;
+        mx = fmaxf(mx, sc[r]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
     float sum = 0.f;
-    for (int i = lane; i < L; i += 64) sum += expf(gat_score(q, piece_slot_src(p, w, i), v) - mx);
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    for (int r = 0; r < R; r++)
+        if (r * 64 + lane < L) sum += expf(sc[r] - mx);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     if (lane != 0) return;
     if (w.w < 0) {
-        float m = q.m[v], S = q.S[v];
-        gat_merge(m, S, mx, sum);
-        q.m[v] = m;
-        q.S[v] = S;
+        gat_update(q, v, d, mx, sum);
     } else {
         const int64_t slot = (int64_t)w.w - p.long_base;
         q.scarry[2 * slot] = mx;
@@ -1748,21 +1773,17 @@ __global__ void k_gat_stats_self(ScatterParams p, GatParams q) {
     if (r >= p.rows) return;
     const int64_t v = p.first_row + r;
     if (p.has_own[v] & OWN_SEGMENT) return;
-    float m = q.m[v], S = q.S[v];
-    gat_merge(m, S, gat_score(q, v, v), 1.f);
-    q.m[v] = m;
-    q.S[v] = S;
+    const float4 d = q.dst[v];
+    gat_update(q, v, d, gat_score(q, v, d.x), 1.f);
 }
 __global__ void k_gat_stats_fixup(ScatterParams p, const int4* __restrict__ fix, int64_t nfix, GatParams q) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= nfix) return;
     const int4 f = fix[t];
-    const int v = f.x;
     const int64_t first = (int64_t)f.y - p.long_base;
-    float m = q.m[v], S = q.S[v];
-    for (int j = 0; j < f.z; j++) gat_merge(m, S, q.scarry[2 * (first + j)], q.scarry[2 * (first + j) + 1]);
-    q.m[v] = m;
-    q.S[v] = S;
+    float4 d = q.dst[f.x];
+    for (int j = 0; j < f.z; j++) gat_merge(d.y, d.z, q.scarry[2 * (first + j)], q.scarry[2 * (first + j) + 1]);
+    q.dst[f.x] = d;
 }
 
 }  // namespace taurus
@@ -1811,9 +1832,9 @@ struct taurus_layer {
     int64_t fix_n = 0;
     uint64_t* mask = nullptr;    // sampled layers: CSR-order mask, drawn when first needed
     std::shared_ptr<taurus::Csc> csc;  // sampled layers: the in-edge lists the sample is drawn from
-    float* gat_hp = nullptr;     // GAT: h' of every vertex, then s, t ([n][ncols])
-    float* gat_m = nullptr;      // GAT: per-destination largest score
-    float* gat_s = nullptr;      // GAT: per-destination sum of exp(score - max)
+    float* gat_hp = nullptr;     // GAT: h' of every vertex ([n][ystride])
+    float* gat_src = nullptr;    // GAT: s of every vertex
+    float4* gat_dst = nullptr;   // GAT: t, largest score, sum of exp(score - max) per destination
     float* gat_carry = nullptr;  // GAT: per hub piece {max, sum}
     const float* gat_attn = nullptr;  // GAT: a_src then a_dst on the device
     bool gat_done = false;       // GAT: passes 2 and 3 have run
@@ -2033,13 +2054,13 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
     const int64_t n = L->n, C = L->C;
     // accumulator width: the perceptron's hidden width for GIN_MLP
     L->d_o = d.agg == TAURUS_GIN_MLP ? d.d_hidden : d.d_out;
-    // GraphSAGE: [W_agg | W_self]; GAT: W and the two attention columns,
-    // padded to a multiple of 4
-    L->ncols = d.agg == TAURUS_SAGE_MEAN ? 2 * d.d_out : d.agg == TAURUS_GAT_ATT ? d.d_out + 4 : L->d_o;
+    // GraphSAGE: [W_agg | W_self]
+    L->ncols = d.agg == TAURUS_SAGE_MEAN ? 2 * d.d_out : L->d_o;
     // Y rows padded to whole 128-byte lines (the padding columns hold the
     // zero-padded weights' products): the transform then writes whole lines
     // and a gathered row starts on a line
-    L->ystride = d.agg == TAURUS_GAT_ATT ? L->ncols : (L->ncols + 31) / 32 * 32;
+    // (GAT keeps every vertex's row: half lines, to bound the table of a narrow output)
+    L->ystride = d.agg == TAURUS_GAT_ATT ? (L->ncols + 15) / 16 * 16 : (L->ncols + 31) / 32 * 32;
     L->shape = scatter_shape(L->d_o);
     L->shape.max_blocks = scatter_resident_blocks(L->shape, false);
     L->shape.max_blocks_att = scatter_resident_blocks(L->shape, true);
@@ -2116,21 +2137,11 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
     std::vector<float> packed32;
     std::vector<uint16_t> packed16;
     size_t wbytes = 0;
-    const float* wsrc = d.weight;
-    std::vector<float> wext;
-    if (d.agg == TAURUS_GAT_ATT) {
-        // [W^T | 0 0 0 0]: the four extra columns of h' (the two attention
-        // terms and padding) are filled after the transform
-        wext.assign((size_t)d.d_in * L->ncols, 0.0f);
-        for (int i = 0; i < d.d_in; i++)
-            for (int o = 0; o < d.d_out; o++) wext[(size_t)i * L->ncols + o] = d.weight[(size_t)i * d.d_out + o];
-        wsrc = wext.data();
-    }
     if (d.in_dtype == TAURUS_F32) {
-        gemm_pack_weights_f32(wsrc, d.d_in, L->ncols, packed32);
+        gemm_pack_weights_f32(d.weight, d.d_in, L->ncols, packed32);
         wbytes = packed32.size() * 4;
     } else {
-        gemm_pack_weights_16(wsrc, d.d_in, L->ncols, d.in_dtype, packed16);
+        gemm_pack_weights_16(d.weight, d.d_in, L->ncols, d.in_dtype, packed16);
         wbytes = packed16.size() * 2;
     }
     wbytes = (wbytes + 255) / 256 * 256;
@@ -2180,10 +2191,9 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
     if (std::min<int64_t>(C, n) * (int64_t)L->ystride * 4 > (int64_t)0x7f000000)
         fail(TAURUS_E_INVALID, "chunk %lld x %d transform columns exceeds 2 GiB of fp32", (long long)C, L->ystride);
     if (d.agg == TAURUS_GAT_ATT) {
-        L->gat_hp = L->arena.alloc<float>(n * (int64_t)L->ncols, "GAT transformed rows and scores");
-        L->gat_m = L->arena.alloc<float>(n, "GAT largest scores");
-        L->gat_s = L->arena.alloc<float>(n, "GAT score sums");
-        fill_i32(reinterpret_cast<int32_t*>(L->gat_s), n, 0, s);
+        L->gat_hp = L->arena.alloc<float>(n * (int64_t)L->ystride, "GAT transformed rows");
+        L->gat_src = L->arena.alloc<float>(n, "GAT source terms");
+        L->gat_dst = L->arena.alloc<float4>(n, "GAT destination terms and score statistics");
         L->gat_carry = L->arena.alloc<float>(2 * std::max<int64_t>(1, idx.max_long_per_chunk), "GAT piece statistics");
     } else {
         L->Y = L->arena.alloc<float>(std::min<int64_t>(C, n) * (int64_t)L->ystride, "chunk transform");
@@ -2519,7 +2529,7 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
     }
     const float* rscale = L->n_out ? L->n_out + b : nullptr;
     // GAT: the first pass only, into the layer's table of transformed rows
-    float* ydst = L->gat_hp ? L->gat_hp + b * (int64_t)L->ncols : L->Y;
+    float* ydst = L->gat_hp ? L->gat_hp + b * (int64_t)L->ystride : L->Y;
     SelfFlush sf{};
     if (L->self_in_transform) {
         sf.own = idx.has_own;
@@ -2550,7 +2560,8 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
     }
     if (ev[1]) TAURUS_HIP(hipEventRecord(ev[1], s));
     if (L->gat_hp) {  // the attention terms of the chunk's rows; passes 2 and 3 run at finalize
-        k_gat_scores<<<(unsigned)ceil_div(e - b, 4), 256, 0, s>>>(ydst, e - b, L->ncols, L->d_o, L->gat_attn);
+        k_gat_scores<<<(unsigned)ceil_div(e - b, 16), 256, 0, s>>>(ydst, e - b, L->ystride, L->d_o, L->gat_attn,
+                                                                  L->gat_src + b, L->gat_dst + b);
         TAURUS_CHECK_LAUNCH();
         if (ev[2]) TAURUS_HIP(hipEventRecord(ev[2], s));
         if (ev[3]) TAURUS_HIP(hipEventRecord(ev[3], s));
@@ -2617,19 +2628,16 @@ static void run_gat_passes(taurus_layer* L) {
     hipStream_t s = L->s;
     const ChunkIndex& idx = *L->idx;
     GatParams q;
-    q.hp = L->gat_hp;
-    q.ystride = L->ncols;
-    q.d_o = L->d_o;
-    q.m = L->gat_m;
-    q.S = L->gat_s;
+    q.src = L->gat_src;
+    q.dst = L->gat_dst;
     q.scarry = L->gat_carry;
     auto params = [&](int64_t k) {
         const int64_t b = k * L->C, e = std::min(b + L->C, L->n);
         ScatterParams p{};
-        p.Y = L->gat_hp + b * (int64_t)L->ncols;
-        p.ystride = L->ncols;
+        p.Y = L->gat_hp + b * (int64_t)L->ystride;
+        p.ystride = L->ystride;
         p.self_col = 0;
-        p.y_bytes = (int)((e - b) * (int64_t)L->ncols * 4);
+        p.y_bytes = (int)((e - b) * (int64_t)L->ystride * 4);
         p.src = idx.item_src ? idx.item_src + idx.chunk_off[(size_t)k] : nullptr;
         p.has_own = idx.has_own;
         p.cnt = L->cnt;
@@ -2646,9 +2654,8 @@ static void run_gat_passes(taurus_layer* L) {
         p.long_base = idx.list_off[NCLASS][(size_t)k];
         p.first_row = b;
         p.rows = e - b;
-        p.att_t = L->gat_hp + L->d_o + 1;
-        p.att_m = L->gat_m;
-        p.att_s = L->gat_s;
+        p.att_src = L->gat_src + b;
+        p.att_dst = L->gat_dst;
         return p;
     };
     auto units = [&](int64_t k, int64_t& nshort) {
