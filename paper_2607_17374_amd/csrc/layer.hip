@@ -313,7 +313,13 @@ __device__ inline SegUnit seg_unit(const uint64_t* keys, const int64_t* seg_star
 }
 
 // ---- work lists by tiles of segments ----
-constexpr int LT_THREADS = 256, LT_PER = 16, LT_TILE = LT_THREADS * LT_PER;
+// A tile is `per` rounds of LT_THREADS segments: up to LT_PER where segments
+// are many, one where they are few (30K segments in tiles of 4,096 kept eight
+// workgroups busy for 16 dependent rounds: 50 us, 6 us with one).
+constexpr int LT_THREADS = 256, LT_PER = 16, LT_MIN_TILES = 1024;
+static int list_tile_rounds(int64_t P) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(LT_PER, P / ((int64_t)LT_THREADS * LT_MIN_TILES)));
+}
 
 // entries segment s adds to every list
 __device__ inline void seg_entries(int64_t slots, int64_t (&c)[NLIST]) {
@@ -328,13 +334,14 @@ __device__ inline void seg_entries(int64_t slots, int64_t (&c)[NLIST]) {
 }
 
 // tile_cnt[l * ntiles + t] = entries the segments of tile t add to list l
-// (the tile's segments in LT_PER rounds of LT_THREADS consecutive ones)
+// (the tile's segments in `per` rounds of LT_THREADS consecutive ones)
 __global__ __launch_bounds__(LT_THREADS) void k_list_tile_counts(const int32_t* __restrict__ slots_of, int64_t P,
-                                                                int64_t ntiles, uint64_t* __restrict__ tile_cnt) {
+                                                                int per, int64_t ntiles,
+                                                                uint64_t* __restrict__ tile_cnt) {
     __shared__ int64_t part[LT_THREADS / 64][NLIST];
     int64_t c[NLIST] = {};
-    const int64_t s0 = (int64_t)blockIdx.x * LT_TILE + threadIdx.x;
-    for (int j = 0; j < LT_PER; j++)
+    const int64_t s0 = (int64_t)blockIdx.x * per * LT_THREADS + threadIdx.x;
+    for (int j = 0; j < per; j++)
         if (s0 + j * LT_THREADS < P) seg_entries(slots_of[s0 + j * LT_THREADS], c);
 #pragma unroll
     for (int l = 0; l < NLIST; l++)
@@ -351,7 +358,7 @@ __global__ __launch_bounds__(LT_THREADS) void k_list_tile_counts(const int32_t* 
 
 // Units of tile t's segments, in segment order within each list, from the
 // tile's positions tile_off[l * ntiles + t] (absolute in the work-list
-// buffer).  The tile is taken in LT_PER rounds of LT_THREADS consecutive
+// buffer).  The tile is taken in `per` rounds of LT_THREADS consecutive
 // segments, one per thread, so reads and each list's writes are
 // contiguous over the threads; a round's positions are a workgroup prefix
 // of the entries its segments add (ballots for the one-entry lists, a scan
@@ -361,7 +368,7 @@ __global__ __launch_bounds__(LT_THREADS) void k_list_tile_counts(const int32_t* 
 // the chunks after it and for k = nchunks.
 __global__ __launch_bounds__(LT_THREADS) void k_list_emit(const uint64_t* __restrict__ keys,
                                                          const int64_t* __restrict__ seg_start,
-                                                         const int32_t* __restrict__ slots_of, int64_t P,
+                                                         const int32_t* __restrict__ slots_of, int64_t P, int per,
                                                          int64_t ntiles, const uint64_t* __restrict__ tile_off,
                                                          int vbits, int kshift, int64_t C,
                                                          const int64_t* __restrict__ chunk_off,
@@ -373,8 +380,8 @@ __global__ __launch_bounds__(LT_THREADS) void k_list_emit(const uint64_t* __rest
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t lt = (1ull << lane) - 1ull;
     if (threadIdx.x < NLIST) run[threadIdx.x] = (int64_t)tile_off[(int64_t)threadIdx.x * ntiles + blockIdx.x];
-    const int64_t t0 = (int64_t)blockIdx.x * LT_TILE;
-    for (int r = 0; r < LT_PER; r++) {
+    const int64_t t0 = (int64_t)blockIdx.x * per * LT_THREADS;
+    for (int r = 0; r < per; r++) {
         const int64_t sg = t0 + (int64_t)r * LT_THREADS + threadIdx.x;
         if (t0 + (int64_t)r * LT_THREADS >= P) break;  // uniform over the workgroup
         const int par = r & 1;
@@ -1557,14 +1564,15 @@ static std::shared_ptr<ChunkIndex> build_index(const taurus_graph& g, int64_t C,
     TAURUS_CHECK_LAUNCH();
     k_self_first<<<(unsigned)ceil_div(n, T), T, 0, s>>>(first_chunk, n, C, idx->has_own);
     TAURUS_CHECK_LAUNCH();
-    // Unit positions: per tile of LT_TILE segments, the entries each list
+    // Unit positions: per tile of segments, the entries each list
     // takes (one pass), an exclusive scan over all lists' tiles one list
     // after another (the lists' buffer positions), then each tile writes its
     // units and its chunks' first positions (a second pass).
-    const int64_t ntiles = ceil_div(P, LT_TILE);
+    const int per = list_tile_rounds(P);
+    const int64_t ntiles = ceil_div(P, (int64_t)per * LT_THREADS);
     uint64_t* tile_cnt = tmp.alloc<uint64_t>(ntiles * NLIST, "list entries per tile");
     uint64_t* tile_off = tmp.alloc<uint64_t>(ntiles * NLIST + 1, "list positions per tile");
-    k_list_tile_counts<<<(unsigned)ntiles, LT_THREADS, 0, s>>>(slots_of, P, ntiles, tile_cnt);
+    k_list_tile_counts<<<(unsigned)ntiles, LT_THREADS, 0, s>>>(slots_of, P, per, ntiles, tile_cnt);
     TAURUS_CHECK_LAUNCH();
     scan_u64(tile_cnt, tile_off, ntiles * NLIST, true, tmp, s);
     int64_t list_base[NLIST + 1] = {0};
@@ -1580,7 +1588,7 @@ static std::shared_ptr<ChunkIndex> build_index(const taurus_graph& g, int64_t C,
     if (total_units >= ((int64_t)1 << 31)) fail(TAURUS_E_INVALID, "too many work units");
     idx->units = idx->arena.alloc<int4>(std::max<int64_t>(1, total_units), "work lists");
     int64_t* dbases = tmp.alloc<int64_t>((nch + 1) * NLIST, "chunk list positions");
-    k_list_emit<<<(unsigned)ntiles, LT_THREADS, 0, s>>>(keys, seg_start, slots_of, P, ntiles, tile_off, vbits,
+    k_list_emit<<<(unsigned)ntiles, LT_THREADS, 0, s>>>(keys, seg_start, slots_of, P, per, ntiles, tile_off, vbits,
                                                        kshift, C, doffs, first_chunk, nch, idx->units, dbases);
     TAURUS_CHECK_LAUNCH();
     {
@@ -1625,9 +1633,9 @@ constexpr float GAT_SLOPE = ATT_SLOPE;
 // The attention terms live in arrays of their own, 20 bytes a vertex, and
 // not beside the rows of h': the statistics then read 4 bytes of a compact
 // array per message instead of a cache line of the table, and rows of h' keep
-// whole 64-byte pieces (500K vertices, 10M edges, 128 -> 64: statistics 394 -> 285 us, scores 90 ->
-// 43 us, aggregation 686 -> 629 us, transform 211 -> 144 us, which lost a
-// column group; a layer 1.60 -> 1.25 ms).
+// whole 64-byte pieces (500K vertices, 10M edges, 128 -> 64: statistics 394
+// -> 285 us, scores 90 -> 43 us, aggregation 686 -> 629 us, transform, which
+// lost a column group, 211 -> 144 us; a layer 1.60 -> 1.25 ms).
 struct GatParams {
     const float* src;  // [n] s_u
     float4* dst;       // [n] {t_v, running largest score, running sum of exp(score - largest) (0 = none yet), -}
