@@ -635,11 +635,26 @@ __global__ __launch_bounds__(RS_THREADS) void k_radix_hist(const K* __restrict__
 #pragma unroll
     for (int q = 0; q < Q; q++) h[q * RS_THREADS + threadIdx.x] = 0;
     const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+    // 16 bytes of keys a load (the order within a tile does not matter here;
+    // tiles start 16-byte aligned): 48M 64-bit keys 116 us by single keys,
+    // 89 us this way
+    constexpr int W = 16 / sizeof(K);
     uint32_t d[RS_ITEMS];
+    if (base + RS_TILE <= n) {  // uniform over the workgroup
 #pragma unroll
-    for (int r = 0; r < RS_ITEMS; r++) {
-        const int64_t g = base + r * RS_THREADS + threadIdx.x;
-        d[r] = g < n ? (uint32_t)((keys[g] >> shift) & MASK) : (uint32_t)NB;
+        for (int r = 0; r < RS_ITEMS / W; r++) {
+            K k[W];
+            *reinterpret_cast<uint4*>(k) =
+                *reinterpret_cast<const uint4*>(keys + base + ((int64_t)r * RS_THREADS + threadIdx.x) * W);
+#pragma unroll
+            for (int i = 0; i < W; i++) d[r * W + i] = (uint32_t)((k[i] >> shift) & MASK);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < RS_ITEMS; r++) {
+            const int64_t g = base + r * RS_THREADS + threadIdx.x;
+            d[r] = g < n ? (uint32_t)((keys[g] >> shift) & MASK) : (uint32_t)NB;
+        }
     }
     __syncthreads();
 #pragma unroll
