@@ -85,12 +85,38 @@ __global__ void k_row_offsets(const uint64_t* __restrict__ keys, int64_t e, int6
     if (u > n) return;
     row_off[u] = first_key_at_least(keys, e, (uint64_t)u << vbits);
 }
-// the rows k_unpack_cols left at -1 (long runs of empty rows)
-__global__ void k_row_offsets_fill(const uint64_t* __restrict__ keys, int64_t e, int64_t n, int vbits,
-                                   int64_t* __restrict__ row_off) {
+// The rows k_unpack_cols left at -1 (long runs of empty rows): an empty row
+// starts where the next one with an entry does.  A lane takes the next
+// written row of its wave; the lanes past the wave's last one share one
+// 64-ary search by the whole wave (a binary search per lane: 56 us at 3M rows
+// and 48M edges, one per wave 52, all of it its 26 dependent loads; 26 us
+// this way).
+__global__ __launch_bounds__(256) void k_row_offsets_fill(const uint64_t* __restrict__ keys, int64_t e, int64_t n,
+                                                          int vbits, int64_t* __restrict__ row_off) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u > n || row_off[u] >= 0) return;
-    row_off[u] = first_key_at_least(keys, e, (uint64_t)u << vbits);
+    const int lane = threadIdx.x & 63;
+    const int64_t x = u <= n ? row_off[u] : 0;
+    const uint64_t written = __ballot(u <= n && x >= 0), todo = __ballot(u <= n && x < 0);
+    if (!todo) return;  // uniform over the wave
+    int64_t end = 0;  // first entry past the wave's rows
+    const uint64_t tail = written ? ~((2ull << (63 - __builtin_clzll(written))) - 1ull) : ~0ull;
+    if (todo & tail) {  // uniform: rows past the wave's last written one
+        const uint64_t target = (uint64_t)(u - lane + 64) << vbits;
+        int64_t lo = 0, hi = e;  // the first position with key >= target lies in [lo, hi]
+        while (hi > lo) {
+            const int64_t step = (hi - lo + 63) >> 6;
+            const int64_t p = lo + (int64_t)(lane + 1) * step - 1;
+            const int k = __popcll(__ballot(p < hi && keys[p] < target));  // whole steps below the target
+            lo += (int64_t)k * step;
+            hi = min(hi, lo + step - 1);
+        }
+        end = lo;
+    }
+    const uint64_t after = written & ~((2ull << lane) - 1ull);
+    const int from = after ? __builtin_ctzll(after) : lane;
+    const int64_t next = __shfl(x, from);
+    if (!((todo >> lane) & 1)) return;
+    row_off[u] = after ? next : end;
 }
 
 // Enqueues the build with every temporary from `arena`; returns the device
