@@ -822,14 +822,21 @@ def bench_sage3_100m(args):
 
     profile = 0 if args.no_profile else 2
     for _ in range(args.warmup):
-        layers_pass(profile)
+        layers_pass(0)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    # events around the scatter launches in the first timed pass only: each
-    # event pair costs about 6 us of the step
-    runs = [layers_pass(profile if i == 0 else 0) for i in range(args.steps)]
+    runs = [layers_pass(0) for _ in range(args.steps)]
     torch.cuda.synchronize()
     layers_ms = (time.perf_counter() - t0) * 1e3 / args.steps
+    # the timed passes aggregate these sampled layers by destination; a
+    # profiled layer broadcasts its chunks, which is what the scatter figures
+    # describe, in an untimed pass (the two need blocks of other sizes, so
+    # cached ones go back to the runtime in between)
+    prof_pass = []
+    if profile:
+        T.release_cached_memory(0)
+        prof_pass = layers_pass(profile)
+        T.release_cached_memory(0)
     ms_step = csr_ms + layers_ms
     say(f"layers {layers_ms:.1f} ms per pass")
 
@@ -842,7 +849,7 @@ def bench_sage3_100m(args):
         d_o, d_in = specs[li]["d_out"], specs[li]["d_in"]
         ob = 4 if specs[li]["out_dtype"] == F.F32 else 2
         wall = float(np.mean([x["wall_ms"] for x in sts]))
-        prof = sts[:1] if profile else []  # the pass with events (and the self-message counts)
+        prof = [prof_pass[li]] if profile else []  # the pass with events (and the self-message counts)
         kb = sampled_scatter_bytes(prof[0], w.n, d_o, ob, sage=True) if prof else None
         ms_sc = float(np.mean([x["ms_scatter"] for x in prof])) if prof else 0.0
         if prof:
@@ -870,7 +877,8 @@ def bench_sage3_100m(args):
                     "traffic": None if args.scale > 1 or args.chunk > 0 else profiled_traffic(w.name),
                     "kernel": "k_scatter",
                     "avg_launch_us": round(sc_ms * 1e3 / sc_launches, 2),
-                    "bytes_per_launch": round(sc_bytes / sc_launches, 0)}
+                    "bytes_per_launch": round(sc_bytes / sc_launches, 0),
+                    "note": "untimed profiled pass, which broadcasts the layers' chunks"}
 
     # ---- untimed pass with events around every kernel (transform figures),
     # copying out the rows the oracle sample reads
@@ -904,7 +912,10 @@ def bench_sage3_100m(args):
                 got_rows[("in", li + 2)] = out.index_select(0, torch.from_numpy(need_rows[li + 2]).to(dev)).cpu()
             got_rows[("out", li + 1)] = out.index_select(0, torch.from_numpy(ids[li]).to(dev)).cpu()
 
-    per = layers_pass(1, hook) if (need_rows or not args.no_profile) else []
+    if need_rows:
+        layers_pass(0, hook)  # the rows checked are those of the path that was timed
+    T.release_cached_memory(0)
+    per = layers_pass(1) if not args.no_profile else []
     gf = gb = gms = 0.0
     for li, st in enumerate(per):
         d_in, d_o = specs[li]["d_in"], specs[li]["d_out"]

@@ -1865,10 +1865,6 @@ struct taurus_layer {
     void* wpack_any = nullptr;  // packed weights (fp32 or 16-bit fragments)
     void* out_dev = nullptr;    // desc.out as kernels address it
     std::unique_ptr<taurus::Residency> res;  // accumulator pool under a budget (null: dense rows)
-    // budgeted layers: the chunk's transform runs here, beside the residency
-    // step on the layer's stream (neither reads what the other writes)
-    hipStream_t side_stream = nullptr;
-    hipEvent_t side_from = nullptr, side_done = nullptr;
     // host-resident chunks: two device staging buffers filled on a copy stream
     hipStream_t copy_stream = nullptr;
     void* stage[2] = {nullptr, nullptr};
@@ -1917,12 +1913,6 @@ static void timing_event_release(hipEvent_t ev) {
 
 taurus_layer::~taurus_layer() {
     for (auto ev : events) taurus::timing_event_release(ev);
-    if (side_stream) {
-        (void)hipStreamSynchronize(side_stream);
-        if (side_from) (void)hipEventDestroy(side_from);
-        if (side_done) (void)hipEventDestroy(side_done);
-        (void)hipStreamDestroy(side_stream);
-    }
     if (copy_stream) {
         (void)hipStreamSynchronize(copy_stream);
         for (int i = 0; i < 2; i++) {
@@ -2387,7 +2377,7 @@ static void gather_to_scatter(taurus_layer* L) {
 // buffer is refilled only after the transform that read it; the caller's x
 // must stay valid until the next call returns, so the previous chunk's copy
 // is waited for here.
-static const void* stage_host_chunk(taurus_layer* L, const void* x, int64_t rows, hipStream_t reader) {
+static const void* stage_host_chunk(taurus_layer* L, const void* x, int64_t rows) {
     hipPointerAttribute_t attr;
     if (hipPointerGetAttributes(&attr, x) != hipSuccess || attr.type != hipMemoryTypeHost) {
         (void)hipGetLastError();
@@ -2410,7 +2400,7 @@ static const void* stage_host_chunk(taurus_layer* L, const void* x, int64_t rows
     if (L->stage_used[cur]) TAURUS_HIP(hipStreamWaitEvent(L->copy_stream, L->gemm_done[cur], 0));
     TAURUS_HIP(hipMemcpyAsync(L->stage[cur], x, bytes, hipMemcpyHostToDevice, L->copy_stream));
     TAURUS_HIP(hipEventRecord(L->h2d_done[cur], L->copy_stream));
-    TAURUS_HIP(hipStreamWaitEvent(reader, L->h2d_done[cur], 0));
+    TAURUS_HIP(hipStreamWaitEvent(L->s, L->h2d_done[cur], 0));
     // the previous chunk's x is released to the caller once its copy is done;
     // waiting after this chunk's copy is queued keeps the copy engine busy
     if (L->stage_used[prev]) TAURUS_HIP(hipEventSynchronize(L->h2d_done[prev]));
@@ -2488,7 +2478,7 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
     if (L->gather) {
         const int64_t row = (int64_t)L->d.d_in * (L->d.in_dtype == TAURUS_F32 ? 4 : 2);
         if (!L->table) L->table = static_cast<char*>(L->arena.alloc_bytes(L->n * row, "input rows"));
-        if (x_on_host) x = stage_host_chunk(L, x, e - b, s);
+        if (x_on_host) x = stage_host_chunk(L, x, e - b);
         gather_copy_rows(x, L->table + b * row, (e - b) * row, s);
         if (x_on_host) TAURUS_HIP(hipEventRecord(L->gemm_done[(L->host_pushes - 1) & 1], s));
         L->pushed[(size_t)k] = 1;
@@ -2497,24 +2487,7 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
         return;
     }
     const ChunkIndex& idx = *L->idx;
-    // The transform's stream.  A budgeted layer's residency step is a dozen
-    // short kernels that leave the matrix cores idle: the transform runs
-    // beside them, from the end of the chunk before, and its copy from the
-    // host is waited for there alone (262K vertices in 2,048-vertex chunks:
-    // 20.6 ms a layer one after the other, 18.6 ms side by side).  Profiled
-    // layers time the launches one by one and keep one stream.
-    hipStream_t ts = s;
-    if (L->res && !L->d.profile) {
-        if (!L->side_stream) {
-            TAURUS_HIP(hipStreamCreateWithFlags(&L->side_stream, hipStreamNonBlocking));
-            TAURUS_HIP(hipEventCreateWithFlags(&L->side_from, hipEventDisableTiming));
-            TAURUS_HIP(hipEventCreateWithFlags(&L->side_done, hipEventDisableTiming));
-        }
-        ts = L->side_stream;
-        TAURUS_HIP(hipEventRecord(L->side_from, s));
-        TAURUS_HIP(hipStreamWaitEvent(ts, L->side_from, 0));
-    }
-    if (x_on_host) x = stage_host_chunk(L, x, e - b, ts);
+    if (x_on_host) x = stage_host_chunk(L, x, e - b);
     // profile 1: events around every kernel; profile 2: around the scatter
     // launch only (ev[1] and ev[2])
     hipEvent_t ev[EV_PER_CHUNK] = {};
@@ -2557,15 +2530,11 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
                              ydst, L->fix_p, L->fix_list, L->fix_n, s);
         L->fix_pending = false;
     } else if (L->d.in_dtype == TAURUS_F32)
-        gemm_f32(static_cast<const float*>(x), e - b, L->d.d_in, L->wpack, L->ystride, rscale, ydst, sfp, ts);
+        gemm_f32(static_cast<const float*>(x), e - b, L->d.d_in, L->wpack, L->ystride, rscale, ydst, sfp, s);
     else
         gemm_16(static_cast<const uint16_t*>(x), L->d.in_dtype, e - b, L->d.d_in,
-                static_cast<const uint16_t*>(L->wpack_any), L->ystride, rscale, ydst, sfp, ts);
-    if (x_on_host) TAURUS_HIP(hipEventRecord(L->gemm_done[(L->host_pushes - 1) & 1], ts));
-    if (ts != s) {
-        TAURUS_HIP(hipEventRecord(L->side_done, ts));
-        TAURUS_HIP(hipStreamWaitEvent(s, L->side_done, 0));
-    }
+                static_cast<const uint16_t*>(L->wpack_any), L->ystride, rscale, ydst, sfp, s);
+    if (x_on_host) TAURUS_HIP(hipEventRecord(L->gemm_done[(L->host_pushes - 1) & 1], s));
     if (ev[1]) TAURUS_HIP(hipEventRecord(ev[1], s));
     if (L->gat_hp) {  // the attention terms of the chunk's rows; passes 2 and 3 run at finalize
         k_gat_scores<<<(unsigned)ceil_div(e - b, 16), 256, 0, s>>>(ydst, e - b, L->ystride, L->d_o, L->gat_attn,
