@@ -424,8 +424,8 @@ void taurus_plan_destroy(taurus_plan* plan);
  * destination instead: it keeps the sample as in-edge lists, its pushes copy
  * x into a table of all rows (allocated by the first push), and
  * taurus_finalize evaluates every destination whose messages have all been
- * pushed.  If its first chunk comes from the host it is broadcast like the
- * others.  *out receives the handle.  Blocks until the index is built.
+ * pushed.  If its first chunk comes from the host, or the device cannot hold
+ * the table, it is broadcast like the others.  *out receives the handle.  Blocks until the index is built.
  * Errors: TAURUS_E_INVALID for bad arguments or a graph that is not a valid
  * simple CSR; TAURUS_E_BUDGET when the budget cannot hold the layer;
  * TAURUS_E_OOM / TAURUS_E_DEVICE from the runtime.  On error *out is NULL.

@@ -1858,6 +1858,7 @@ struct taurus_layer {
     bool gather = false, gathered = false;
     taurus::SampleLists lists;       // kept in-edges by destination
     char* table = nullptr;           // [n][d_in] of in_dtype, allocated by the first push
+    float* partial = nullptr;        // and the aggregate's products where the kernels split (gather_partial_rows)
     int* gather_bad = nullptr;       // sampler flags, read at finalize
     uint32_t* gather_ord = nullptr;  // the order destinations are taken in
     unsigned long long* list_counts = nullptr;
@@ -2359,7 +2360,8 @@ static void layer_init(taurus_layer* L) {
 
 // A gathered layer whose first chunk comes from the host is broadcast after
 // all: each chunk's messages then overlap the next chunk's copy, where a
-// gather would only start after the last copy.
+// gather would only start after the last copy.  So is one whose table the
+// device cannot hold.
 static void gather_to_scatter(taurus_layer* L) {
     L->d.weight = L->w_host.data();
     L->d.bias = L->b_host.empty() ? nullptr : L->b_host.data();
@@ -2367,6 +2369,12 @@ static void gather_to_scatter(taurus_layer* L) {
     L->gather = false;
     L->n_out = nullptr;
     scatter_init(L, L->s, &L->lists);
+    L->arena.free_ptr(L->lists.off);
+    L->arena.free_ptr(L->lists.src);
+    if (L->gather_ord) L->arena.free_ptr(L->gather_ord);
+    L->lists.off = nullptr;
+    L->lists.src = nullptr;
+    L->gather_ord = nullptr;
     L->d.weight = L->d.bias = nullptr;
     L->w_host = {};
     L->b_host = {};
@@ -2460,6 +2468,47 @@ static void transform_with_fixup(const ScatterShape& sh, const float* X, int64_t
     fail(TAURUS_E_INVALID, "unsupported row shape G=%d VEC=%d", sh.G, sh.VEC);
 }
 
+static GatherArgs gather_args(const taurus_layer* L) {
+    const taurus_layer_desc& d = L->d;
+    GatherArgs a{};
+    a.X = L->table;
+    a.n = L->n;
+    a.K = d.d_in;
+    a.off = L->lists.off;
+    a.src = L->lists.src;
+    a.W = L->wpack_any;
+    a.NBP = gather_blocks_n(d.d_out);
+    a.bias = L->bias;
+    a.norm = L->n_out;
+    a.out = L->out_dev;
+    a.d_o = d.d_out;
+    a.out_dtype = d.out_dtype;
+    a.relu = d.relu;
+    a.sage = d.agg == TAURUS_SAGE_MEAN ? 1 : 0;
+    a.order = L->gather_ord;
+    a.nonzero = L->lists.nonzero;
+    a.partial = L->partial;
+    a.pairs = d.out_dtype != TAURUS_F32 ? 1 : 0;
+    return a;
+}
+
+// The first push's allocations of a gathered layer; false when the device
+// cannot hold them (the broadcast needs less where inputs are wide or the
+// kernels split).
+static bool gather_alloc(taurus_layer* L, int64_t row) {
+    try {
+        L->table = static_cast<char*>(L->arena.alloc_bytes(L->n * row, "input rows"));
+        const int64_t rows = gather_partial_rows(gather_args(L), L->d.in_dtype);
+        if (rows > 0) L->partial = L->arena.alloc<float>(rows * L->d.d_out, "aggregate products");
+        return true;
+    } catch (const Failure& f) {
+        if (f.status != TAURUS_E_OOM) throw;
+        if (L->table) L->arena.free_ptr(L->table);
+        L->table = nullptr;
+        return false;
+    }
+}
+
 static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int32_t x_on_host) {
     if (L->poisoned) fail(TAURUS_E_STATE, "layer handle is poisoned by an earlier failure");
     if (b < 0 || e > L->n || b >= e || b % L->C != 0 || e != std::min(b + L->C, L->n))
@@ -2474,10 +2523,9 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
         L->acc_deferred = false;
     }
     hipStream_t s = L->s;
-    if (L->gather && x_on_host && !L->table) gather_to_scatter(L);
+    const int64_t row = (int64_t)L->d.d_in * (L->d.in_dtype == TAURUS_F32 ? 4 : 2);
+    if (L->gather && !L->table && (x_on_host || !gather_alloc(L, row))) gather_to_scatter(L);
     if (L->gather) {
-        const int64_t row = (int64_t)L->d.d_in * (L->d.in_dtype == TAURUS_F32 ? 4 : 2);
-        if (!L->table) L->table = static_cast<char*>(L->arena.alloc_bytes(L->n * row, "input rows"));
         if (x_on_host) x = stage_host_chunk(L, x, e - b);
         gather_copy_rows(x, L->table + b * row, (e - b) * row, s);
         if (x_on_host) TAURUS_HIP(hipEventRecord(L->gemm_done[(L->host_pushes - 1) & 1], s));
@@ -2697,27 +2745,8 @@ static int finalize_gather(taurus_layer* L, taurus_stats* st) {
         gather_ready(L->lists.off, L->lists.src, L->n, L->C, pushed, ready, dleft, s);
     }
     if (L->table && !L->gathered) {
-        GatherArgs a{};
-        a.X = L->table;
-        a.n = L->n;
-        a.K = d.d_in;
-        a.off = L->lists.off;
-        a.src = L->lists.src;
-        a.W = L->wpack_any;
-        a.NBP = gather_blocks_n(d.d_out);
-        a.bias = L->bias;
-        a.norm = L->n_out;
-        a.out = L->out_dev;
-        a.d_o = d.d_out;
-        a.out_dtype = d.out_dtype;
-        a.relu = d.relu;
-        a.sage = sage ? 1 : 0;
+        GatherArgs a = gather_args(L);
         a.ready = ready;
-        a.order = L->gather_ord;
-        a.nonzero = L->lists.nonzero;
-        a.pairs = d.out_dtype != TAURUS_F32 ? 1 : 0;
-        const int64_t rows = gather_partial_rows(a, d.in_dtype);
-        if (rows > 0) a.partial = tmp.alloc<float>(rows * d.d_out, "aggregate products");
         gather_layer(a, d.in_dtype, s);
         L->gathered = true;
     }
