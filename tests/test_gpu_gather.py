@@ -215,3 +215,43 @@ def test_values_that_are_not_finite(torch_cuda):
         fin = np.isfinite(z)
         rms = np.sqrt(np.mean(z[fin & (np.abs(z) < 1e30)] ** 2))
         assert np.all(np.abs(y[fin] - z[fin]) <= 2e-5 * (np.abs(z[fin]) + rms))
+
+
+@pytest.mark.parametrize("agg,d_in,d_out,dt,od,k", [
+    (SAGE, 104, 44, BF16, F32, 10),      # both halves' weights resident
+    (SAGE, 256, 172, BF16, F32, 5),      # halves apart, partial products added
+    (SAGE, 128, 256, F32, BF16, 6),      # fp32 weights: halves apart
+    (GCN, 64, 100, F32, F32, 7), (GIN, 128, 260, BF16, BF16, 3)])
+def test_large_layers(torch_cuda, agg, d_in, d_out, dt, od, k):
+    """Enough destinations for the persistent kernels and the order by list
+    length (from 262,144 on), against float64 on the GPU."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n = 300_001
+    print(f"gather large agg={agg} {d_in}->{d_out} dt={dt}/{od} k={k}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    u = torch.randint(0, n, (1_500_000,), generator=g, device="cuda")
+    v = (torch.rand(1_500_000, generator=g, device="cuda") ** 3 * (n - 1)).long()   # many lists empty, some long
+    key = torch.unique((u * n + v)[u != v])
+    row_off, col_dst = T.build_csr(n, (key // n).int(), (key % n).int())
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, d_in, d_out, dt, od, k, chunk=65536)
+    xd = x.cuda()
+    L.push_all(xd)
+    st = L.finalize()
+    words, kept = L.sampled_edges()
+    L.destroy()
+    assert st["completed"] == n and st["messages"] == kept < key.numel()
+    keep = torch.from_numpy(np.unpackbits(words.view(np.uint8), bitorder="little")[:key.numel()].astype(bool)).cuda()
+    u, v = key[keep] // n, key[keep] % n
+    xd, W, b = xd.double(), torch.from_numpy(np.ascontiguousarray(W)).cuda().double(), torch.from_numpy(b).cuda().double()
+    d = torch.bincount(v, minlength=n).double()
+    if agg == SAGE:
+        s = torch.zeros_like(xd).index_add_(0, v, xd[u])
+        z = (s / d.clamp(min=1)[:, None]) @ W[:, :d_out] + xd @ W[:, d_out:]
+    elif agg == GCN:
+        no = (torch.bincount(u, minlength=n) + 1).double().rsqrt()
+        s = torch.zeros_like(xd).index_add_(0, v, xd[u] * no[u][:, None])
+        z = ((s + xd * no[:, None]) * (d + 1).rsqrt()[:, None]) @ W
+    else:
+        z = (torch.zeros_like(xd).index_add_(0, v, xd[u]) + xd) @ W
+    _check(out, torch.relu(z + b).cpu().numpy(), od)
