@@ -2044,13 +2044,8 @@ static void join_setup(taurus_layer* L, hipStream_t s) {
     if (L->res) L->res->arena.set_stream(L->s);
 }
 
-// Set-up of a layer that broadcasts its chunks: chunk index, counts,
-// weights, accumulators.  lists: the kept in-edges of a sampled layer that
-// drew them already.
-static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* lists) {
-    const taurus_graph& g = L->g;
+static void set_widths(taurus_layer* L) {
     const taurus_layer_desc& d = L->d;
-    const int64_t n = L->n, C = L->C;
     // accumulator width: the perceptron's hidden width for GIN_MLP
     L->d_o = d.agg == TAURUS_GIN_MLP ? d.d_hidden : d.d_out;
     // GraphSAGE: [W_agg | W_self]
@@ -2060,6 +2055,21 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
     // and a gathered row starts on a line
     // (GAT keeps every vertex's row: half lines, to bound the table of a narrow output)
     L->ystride = d.agg == TAURUS_GAT_ATT ? (L->ncols + 15) / 16 * 16 : (L->ncols + 31) / 32 * 32;
+}
+
+// the scatter addresses Y with 32-bit byte offsets
+static void check_chunk_bytes(const taurus_layer* L) {
+    if (std::min<int64_t>(L->C, L->n) * (int64_t)L->ystride * 4 > (int64_t)0x7f000000)
+        fail(TAURUS_E_INVALID, "chunk %lld x %d transform columns exceeds 2 GiB of fp32", (long long)L->C, L->ystride);
+}
+
+// Set-up of a layer that broadcasts its chunks: chunk index, counts,
+// weights, accumulators.  lists: the kept in-edges of a sampled layer that
+// drew them already.
+static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* lists) {
+    const taurus_graph& g = L->g;
+    const taurus_layer_desc& d = L->d;
+    const int64_t n = L->n, C = L->C;
     L->shape = scatter_shape(L->d_o);
     L->shape.max_blocks = scatter_resident_blocks(L->shape, false);
     L->shape.max_blocks_att = scatter_resident_blocks(L->shape, true);
@@ -2092,7 +2102,8 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
         L->idx = build_index(g, C, &req, s, 0, scratch.get());
         if (d.agg == TAURUS_GCN_SYM) {
             // the source norms count kept out-edges: the mask in CSR order
-            L->mask = L->arena.alloc<uint64_t>(std::max<int64_t>(1, ceil_div(g.e, 64)), "fanout mask");
+            if (!L->mask)
+                L->mask = L->arena.alloc<uint64_t>(std::max<int64_t>(1, ceil_div(g.e, 64)), "fanout mask");
             sample_mask(g, *L->csc, d.seed, d.layer, d.fanout, L->mask, s);
         }
     } else if (plan) {
@@ -2186,9 +2197,7 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
     }
 
     // working buffers
-    // the scatter addresses Y with 32-bit byte offsets
-    if (std::min<int64_t>(C, n) * (int64_t)L->ystride * 4 > (int64_t)0x7f000000)
-        fail(TAURUS_E_INVALID, "chunk %lld x %d transform columns exceeds 2 GiB of fp32", (long long)C, L->ystride);
+    check_chunk_bytes(L);
     if (d.agg == TAURUS_GAT_ATT) {
         L->gat_hp = L->arena.alloc<float>(n * (int64_t)L->ystride, "GAT transformed rows");
         L->gat_src = L->arena.alloc<float>(n, "GAT source terms");
@@ -2306,7 +2315,6 @@ static bool gather_init(taurus_layer* L, hipStream_t s) {
             L->gather_ord = gather_order(L->lists.off, n, d.fanout, L->arena, tmp, bad, 8, s);
     }
     L->gather = true;
-    L->d_o = d.d_out;
     L->ms_index = ms_since(t_index);
     if (d.agg == TAURUS_GCN_SYM) {
         L->n_out = L->arena.alloc<float>(n, "source norms");
@@ -2315,8 +2323,7 @@ static bool gather_init(taurus_layer* L, hipStream_t s) {
     L->list_counts = L->arena.alloc<unsigned long long>(LIST_COUNTS + 1, "list counts");
     // weights: the aggregate's columns, then GraphSAGE's self columns
     const bool sage = d.agg == TAURUS_SAGE_MEAN;
-    const int ld = sage ? 2 * d.d_out : d.d_out;
-    L->ncols = ld;
+    const int ld = L->ncols;
     L->w_host.assign(d.weight, d.weight + (size_t)d.d_in * ld);
     if (d.bias) L->b_host.assign(d.bias, d.bias + d.d_out);
     std::vector<float> p32;
@@ -2353,7 +2360,12 @@ static void layer_init(taurus_layer* L) {
     const taurus_plan* plan = L->d.plan;
     if (plan && (!same_graph(plan->g, L->g) || plan->chunk != L->C))
         fail(TAURUS_E_INVALID, "plan was built for another graph or chunk size");
-    if (!gather_rule(L->d) || !gather_init(L, s)) scatter_init(L, s, nullptr);
+    set_widths(L);
+    // a gathered layer may still be broadcast (gather_to_scatter): what that
+    // refuses as an argument is refused here
+    const bool gather = gather_rule(L->d);
+    if (gather) check_chunk_bytes(L);
+    if (!gather || !gather_init(L, s)) scatter_init(L, s, nullptr);
     join_setup(L, s);
     L->ms_init = ms_since(t_start);  // host time; the work stays queued on the stream
 }
@@ -2361,14 +2373,21 @@ static void layer_init(taurus_layer* L) {
 // A gathered layer whose first chunk comes from the host is broadcast after
 // all: each chunk's messages then overlap the next chunk's copy, where a
 // gather would only start after the last copy.  So is one whose table the
-// device cannot hold.
+// device cannot hold.  The layer counts as gathered until the switch is
+// complete; a failure on the way leaves neither form whole and poisons the
+// handle, whatever its status.
 static void gather_to_scatter(taurus_layer* L) {
     L->d.weight = L->w_host.data();
     L->d.bias = L->b_host.empty() ? nullptr : L->b_host.data();
     L->d.setup_stream = nullptr;
-    L->gather = false;
     L->n_out = nullptr;
-    scatter_init(L, L->s, &L->lists);
+    try {
+        scatter_init(L, L->s, &L->lists);
+    } catch (...) {
+        L->poisoned = true;
+        throw;
+    }
+    L->gather = false;
     L->arena.free_ptr(L->lists.off);
     L->arena.free_ptr(L->lists.src);
     if (L->gather_ord) L->arena.free_ptr(L->gather_ord);
@@ -2386,11 +2405,6 @@ static void gather_to_scatter(taurus_layer* L) {
 // must stay valid until the next call returns, so the previous chunk's copy
 // is waited for here.
 static const void* stage_host_chunk(taurus_layer* L, const void* x, int64_t rows) {
-    hipPointerAttribute_t attr;
-    if (hipPointerGetAttributes(&attr, x) != hipSuccess || attr.type != hipMemoryTypeHost) {
-        (void)hipGetLastError();
-        fail(TAURUS_E_INVALID, "x_on_host = 1 but x is not pinned host memory");
-    }
     const size_t elem = L->d.in_dtype == TAURUS_F32 ? 4 : 2;
     const size_t bytes = (size_t)rows * (size_t)L->d.d_in * elem;
     if (!L->copy_stream) {
@@ -2518,6 +2532,11 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
     if (x_on_host != 0 && x_on_host != 1) fail(TAURUS_E_INVALID, "x_on_host=%d", x_on_host);
     const int64_t k = b / L->C;
     if (L->pushed[(size_t)k]) fail(TAURUS_E_STATE, "chunk %lld pushed twice", (long long)k);
+    hipPointerAttribute_t attr;
+    if (x_on_host && (hipPointerGetAttributes(&attr, x) != hipSuccess || attr.type != hipMemoryTypeHost)) {
+        (void)hipGetLastError();
+        fail(TAURUS_E_INVALID, "x_on_host = 1 but x is not pinned host memory");
+    }
     if (L->acc_deferred) {
         L->acc = L->arena.alloc<float>(L->n * (int64_t)L->d_o, "accumulators");
         L->acc_deferred = false;

@@ -358,8 +358,17 @@ void Readback::run(hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- arena -----
+// For tests of failure handling: the calling thread's next allocation of
+// device memory named `what` (alloc_bytes) fails as if there were none left.
+static thread_local std::string t_fail_alloc;
+extern "C" void taurus_test_fail_alloc(const char* what) { t_fail_alloc = what ? what : ""; }
+
 void* Arena::alloc_bytes(int64_t bytes, const char* what) {
     if (bytes <= 0) bytes = 16;
+    if (!t_fail_alloc.empty() && t_fail_alloc == what) {
+        t_fail_alloc.clear();
+        fail(TAURUS_E_OOM, "allocation of %lld bytes for %s failed on request", (long long)bytes, what);
+    }
     if (region_) {
         const int64_t start = (top_ + 255) & ~(int64_t)255;
         if (start + bytes <= capacity_ && nstarts_ < REGION_STACK) {

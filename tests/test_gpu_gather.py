@@ -255,3 +255,77 @@ def test_large_layers(torch_cuda, agg, d_in, d_out, dt, od, k):
     else:
         z = (torch.zeros_like(xd).index_add_(0, v, xd[u]) + xd) @ W
     _check(out, torch.relu(z + b).cpu().numpy(), od)
+
+
+def _fail_alloc(what):
+    """The next device allocation of that name on this thread fails."""
+    import paper_2607_17374_amd as T
+    import ctypes
+    f = T.lib().taurus_test_fail_alloc
+    f.restype, f.argtypes = None, [ctypes.c_char_p]
+    f(what.encode() if what else None)
+
+
+def test_oversize_chunk_is_refused_at_init(torch_cuda):
+    """A chunk whose transform would exceed 2 GiB is an argument error of
+    init, also for a layer that would be gathered: the first host chunk would
+    broadcast it."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n = 1_100_000
+    src = torch.arange(0, 999, dtype=torch.int32, device="cuda")
+    row_off, col_dst = T.build_csr(n, src, torch.full_like(src, 999))
+    with pytest.raises(T.TaurusError) as ex:
+        _layer(torch, n, row_off, col_dst, SAGE, 8, 256, BF16, BF16, 2, chunk=1 << 21)
+    assert ex.value.status == -1 and "2 GiB" in str(ex.value)
+
+
+def test_memory_that_is_not_pinned_changes_nothing(torch_cuda):
+    """x_on_host with ordinary memory is refused before the layer's form
+    changes: the layer still gathers device chunks."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, chunk = 1025, 192
+    src, dst, row_off, col_dst = _graph(torch, n, 6000, 3)
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, SAGE, 64, 48, F32, F32, 6, chunk=chunk)
+    assert T.lib().taurus_push_chunk(L._h, 0, chunk, x.data_ptr(), 1) == -1
+    _fail_alloc("work lists")                       # only the broadcast allocates these
+    L.push_all(x.cuda())
+    st = L.finalize()
+    _fail_alloc(None)
+    words, _ = L.sampled_edges()
+    L.destroy()
+    assert st["completed"] == n
+    _check(out, _reference(SAGE, n, src, dst, words, x.double().numpy(), W, b, True, 48), F32)
+
+
+@pytest.mark.parametrize("what", ["index keys", "work lists", "chunk transform", "accumulators"])
+def test_failed_switch_to_the_broadcast_poisons(torch_cuda, what):
+    """A first host chunk whose broadcast cannot be set up: every later push
+    and finalize is refused, nothing is launched, the sample can still be read."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, chunk = 1025, 192
+    src, dst, row_off, col_dst = _graph(torch, n, 6000, 3)
+    L, x, _, _, out = _layer(torch, n, row_off, col_dst, GCN, 64, 48, F32, F32, 6, chunk=chunk)
+    xh, xd = x.pin_memory(), x.cuda()
+    _fail_alloc(what)
+    status = []
+    for _ in range(2):
+        with pytest.raises(T.TaurusError) as ex:
+            L.push_chunk(0, chunk, xh[:chunk])
+        status.append(ex.value.status)
+    _fail_alloc(None)
+    with pytest.raises(T.TaurusError) as ex:
+        L.push_chunk(0, chunk, xd[:chunk])
+    status.append(ex.value.status)
+    with pytest.raises(T.TaurusError) as ex:
+        L.finalize()
+    status.append(ex.value.status)
+    # (the index's temporaries live in the accumulators: "index keys" is carved there)
+    assert status == [-2, -4, -4, -4], status
+    _, kept = L.sampled_edges()
+    assert 0 < kept < len(src)
+    L.destroy()
+    torch.cuda.synchronize()
+    assert bool((out == -7.0).all())
