@@ -2409,14 +2409,21 @@ static const void* stage_host_chunk(taurus_layer* L, const void* x, int64_t rows
     const size_t bytes = (size_t)rows * (size_t)L->d.d_in * elem;
     if (!L->copy_stream) {
         TAURUS_HIP(hipStreamCreateWithFlags(&L->copy_stream, hipStreamNonBlocking));
+        // taken on the copy stream, which then waits for a recycled buffer's
+        // last user and not for all that the layer's stream has queued
+        L->arena.set_stream(L->copy_stream);
+        try {
+            for (auto& st : L->stage)
+                st = L->arena.alloc_bytes((int64_t)(std::min(L->C, L->n) * L->d.d_in * elem), "chunk staging");
+        } catch (...) {
+            L->arena.set_stream(L->s);
+            throw;
+        }
+        L->arena.set_stream(L->s);
         for (int i = 0; i < 2; i++) {
-            L->stage[i] = L->arena.alloc_bytes((int64_t)(std::min(L->C, L->n) * L->d.d_in * elem), "chunk staging");
             TAURUS_HIP(hipEventCreateWithFlags(&L->h2d_done[i], hipEventDisableTiming));
             TAURUS_HIP(hipEventCreateWithFlags(&L->gemm_done[i], hipEventDisableTiming));
         }
-        // the buffers may still be in use by earlier work of the layer's stream
-        TAURUS_HIP(hipEventRecord(L->h2d_done[0], L->s));
-        TAURUS_HIP(hipStreamWaitEvent(L->copy_stream, L->h2d_done[0], 0));
     }
     const int prev = (int)((L->host_pushes + 1) & 1), cur = (int)(L->host_pushes & 1);
     if (L->stage_used[cur]) TAURUS_HIP(hipStreamWaitEvent(L->copy_stream, L->gemm_done[cur], 0));
