@@ -1861,8 +1861,9 @@ struct taurus_layer {
     float* partial = nullptr;        // and the aggregate's products where the kernels split (gather_partial_rows)
     int* gather_bad = nullptr;       // sampler flags, read at finalize
     uint32_t* gather_ord = nullptr;  // the order destinations are taken in
-    unsigned long long* list_counts = nullptr;
-    std::vector<float> w_host, b_host;   // for a layer that turns out to be fed from the host
+    std::vector<float> w_host, b_host;   // desc.weight and desc.bias until the first push
+    hipEvent_t setup_done = nullptr;     // end of a set-up stream's work
+    taurus::Arena gather_arena;          // what gather_prepare takes
     void* wpack_any = nullptr;  // packed weights (fp32 or 16-bit fragments)
     void* out_dev = nullptr;    // desc.out as kernels address it
     std::unique_ptr<taurus::Residency> res;  // accumulator pool under a budget (null: dense rows)
@@ -1914,6 +1915,7 @@ static void timing_event_release(hipEvent_t ev) {
 
 taurus_layer::~taurus_layer() {
     for (auto ev : events) taurus::timing_event_release(ev);
+    if (setup_done) (void)hipEventDestroy(setup_done);
     if (copy_stream) {
         (void)hipStreamSynchronize(copy_stream);
         for (int i = 0; i < 2; i++) {
@@ -2294,58 +2296,113 @@ static bool gather_rule(const taurus_layer_desc& d) {
            d.d_in <= GATHER_MAX_K && in_bytes <= 8 * (int64_t)d.d_out;
 }
 
-// False (nothing set up but the in-edge lists) when the sample keeps every
-// edge: such a layer is the exact layer, and is broadcast like it so that
-// the two agree bit for bit.
+// The sample, and a copy of what either form needs later.  False (nothing set
+// up but the in-edge lists) when the sample keeps every edge: such a layer is
+// the exact layer, and is broadcast like it so that the two agree bit for bit.
 static bool gather_init(taurus_layer* L, hipStream_t s) {
     const taurus_layer_desc& d = L->d;
-    const int64_t n = L->n;
     const auto t_index = std::chrono::steady_clock::now();
     L->csc = layer_csc(L, s, nullptr);
     {
         Arena tmp(s);
         int* bad = L->arena.alloc<int>(1, "sampler flag");
         fill_i32(bad, 1, 0, s);
-        if (!sample_lists(*L->csc, n, L->g.e, d.seed, d.layer, d.fanout, L->arena, tmp, L->lists, bad, s)) {
+        if (!sample_lists(*L->csc, L->n, L->g.e, d.seed, d.layer, d.fanout, L->arena, tmp, L->lists, bad, s)) {
             L->arena.free_ptr(bad);
             return false;
         }
         L->gather_bad = bad;
-        if (n >= GATHER_ORDER_MIN)
-            L->gather_ord = gather_order(L->lists.off, n, d.fanout, L->arena, tmp, bad, 8, s);
     }
     L->gather = true;
     L->ms_index = ms_since(t_index);
-    if (d.agg == TAURUS_GCN_SYM) {
-        L->n_out = L->arena.alloc<float>(n, "source norms");
-        gather_norms(L->lists.src, L->lists.kept, n, L->n_out, s);
-    }
-    L->list_counts = L->arena.alloc<unsigned long long>(LIST_COUNTS + 1, "list counts");
-    // weights: the aggregate's columns, then GraphSAGE's self columns
-    const bool sage = d.agg == TAURUS_SAGE_MEAN;
-    const int ld = L->ncols;
-    L->w_host.assign(d.weight, d.weight + (size_t)d.d_in * ld);
+    L->w_host.assign(d.weight, d.weight + (size_t)d.d_in * L->ncols);
     if (d.bias) L->b_host.assign(d.bias, d.bias + d.d_out);
-    std::vector<float> p32;
-    std::vector<uint16_t> p16;
-    const bool pairs = d.out_dtype != TAURUS_F32;
-    for (int h = 0; h < (sage ? 2 : 1); h++) {
-        if (d.in_dtype == TAURUS_F32) gather_pack_f32(d.weight + h * d.d_out, ld, d.d_in, d.d_out, pairs, p32);
-        else gather_pack_bf16(d.weight + h * d.d_out, ld, d.d_in, d.d_out, pairs, p16);
-    }
-    const size_t wbytes = p32.size() * 4 + p16.size() * 2;  // whole fragments: a multiple of 1 KiB
-    const size_t pbytes = wbytes + (size_t)d.d_out * 4;
-    char* stage = static_cast<char*>(pinned_staging(pbytes));
-    std::memcpy(stage, p32.empty() ? static_cast<const void*>(p16.data()) : p32.data(), wbytes);
-    float* sbias = reinterpret_cast<float*>(stage + wbytes);
-    for (int j = 0; j < d.d_out; j++) sbias[j] = d.bias ? d.bias[j] : 0.0f;
-    L->wpack_any = L->arena.alloc_bytes((int64_t)pbytes, "packed weights and bias");
-    L->bias = reinterpret_cast<float*>(static_cast<char*>(L->wpack_any) + wbytes);
-    TAURUS_HIP(hipMemcpyAsync(L->wpack_any, stage, pbytes, hipMemcpyHostToDevice, s));
-    pinned_staging_in_flight(s);
     L->out_dev = d.out;
     L->pushed.assign((size_t)L->nchunks, 0);
+    if (s != L->s) {
+        TAURUS_HIP(hipEventCreateWithFlags(&L->setup_done, hipEventDisableTiming));
+        TAURUS_HIP(hipEventRecord(L->setup_done, s));
+    }
     return true;
+}
+
+static GatherArgs gather_args(const taurus_layer* L) {
+    const taurus_layer_desc& d = L->d;
+    GatherArgs a{};
+    a.X = L->table;
+    a.n = L->n;
+    a.K = d.d_in;
+    a.off = L->lists.off;
+    a.src = L->lists.src;
+    a.W = L->wpack_any;
+    a.NBP = gather_blocks_n(d.d_out);
+    a.bias = L->bias;
+    a.norm = L->n_out;
+    a.out = L->out_dev;
+    a.d_o = d.d_out;
+    a.out_dtype = d.out_dtype;
+    a.relu = d.relu;
+    a.sage = d.agg == TAURUS_SAGE_MEAN ? 1 : 0;
+    a.order = L->gather_ord;
+    a.nonzero = L->lists.nonzero;
+    a.partial = L->partial;
+    a.pairs = d.out_dtype != TAURUS_F32 ? 1 : 0;
+    return a;
+}
+
+// What only a gathered layer needs, set up by its first device chunk (a first
+// host chunk, which broadcasts the layer, then costs what it would have cost
+// without the gather): table, order, norms, packed weights, partial products.
+// False, holding nothing, when the device cannot hold them (the broadcast
+// needs less where inputs are wide or the kernels split).
+static bool gather_prepare(taurus_layer* L) {
+    const taurus_layer_desc& d = L->d;
+    const int64_t n = L->n, row = (int64_t)d.d_in * (d.in_dtype == TAURUS_F32 ? 4 : 2);
+    hipStream_t s = L->s;
+    Arena& arena = L->gather_arena;
+    arena.set_stream(s);
+    try {
+        L->table = static_cast<char*>(arena.alloc_bytes(n * row, "input rows"));
+        if (n >= GATHER_ORDER_MIN) {
+            Arena tmp(s);
+            L->gather_ord = gather_order(L->lists.off, n, d.fanout, arena, tmp, L->gather_bad, 8, s);
+        }
+        if (d.agg == TAURUS_GCN_SYM) {
+            L->n_out = arena.alloc<float>(n, "source norms");
+            gather_norms(L->lists.src, L->lists.kept, n, L->n_out, s);
+        }
+        // weights: the aggregate's columns, then GraphSAGE's self columns
+        const float* w = L->w_host.data();
+        std::vector<float> p32;
+        std::vector<uint16_t> p16;
+        const bool pairs = d.out_dtype != TAURUS_F32;
+        for (int h = 0; h < (d.agg == TAURUS_SAGE_MEAN ? 2 : 1); h++) {
+            if (d.in_dtype == TAURUS_F32) gather_pack_f32(w + h * d.d_out, L->ncols, d.d_in, d.d_out, pairs, p32);
+            else gather_pack_bf16(w + h * d.d_out, L->ncols, d.d_in, d.d_out, pairs, p16);
+        }
+        const size_t wbytes = p32.size() * 4 + p16.size() * 2;  // whole fragments: a multiple of 1 KiB
+        const size_t pbytes = wbytes + (size_t)d.d_out * 4;
+        char* stage = static_cast<char*>(pinned_staging(pbytes));
+        std::memcpy(stage, p32.empty() ? static_cast<const void*>(p16.data()) : p32.data(), wbytes);
+        float* sbias = reinterpret_cast<float*>(stage + wbytes);
+        for (int j = 0; j < d.d_out; j++) sbias[j] = L->b_host.empty() ? 0.0f : L->b_host[(size_t)j];
+        L->wpack_any = arena.alloc_bytes((int64_t)pbytes, "packed weights and bias");
+        L->bias = reinterpret_cast<float*>(static_cast<char*>(L->wpack_any) + wbytes);
+        TAURUS_HIP(hipMemcpyAsync(L->wpack_any, stage, pbytes, hipMemcpyHostToDevice, s));
+        pinned_staging_in_flight(s);
+        const int64_t rows = gather_partial_rows(gather_args(L), d.in_dtype);
+        if (rows > 0) L->partial = arena.alloc<float>(rows * d.d_out, "aggregate products");
+        return true;
+    } catch (const Failure& f) {
+        if (f.status != TAURUS_E_OOM) throw;
+        arena.release();
+        L->table = nullptr;
+        L->gather_ord = nullptr;
+        L->n_out = nullptr;
+        L->wpack_any = nullptr;
+        L->bias = nullptr;
+        return false;
+    }
 }
 
 static void layer_init(taurus_layer* L) {
@@ -2370,6 +2427,10 @@ static void layer_init(taurus_layer* L) {
     L->ms_init = ms_since(t_start);  // host time; the work stays queued on the stream
 }
 
+static void open_copy_stream(taurus_layer* L) {
+    if (!L->copy_stream) TAURUS_HIP(hipStreamCreateWithFlags(&L->copy_stream, hipStreamNonBlocking));
+}
+
 // A gathered layer whose first chunk comes from the host is broadcast after
 // all: each chunk's messages then overlap the next chunk's copy, where a
 // gather would only start after the last copy.  So is one whose table the
@@ -2379,21 +2440,29 @@ static void layer_init(taurus_layer* L) {
 static void gather_to_scatter(taurus_layer* L) {
     L->d.weight = L->w_host.data();
     L->d.bias = L->b_host.empty() ? nullptr : L->b_host.data();
-    L->d.setup_stream = nullptr;
-    L->n_out = nullptr;
+    hipStream_t s = L->s;
     try {
-        scatter_init(L, L->s, &L->lists);
+        if (L->setup_done) {
+            // init was given a set-up stream: what the layer's stream still
+            // has queued does not hold this set-up up either
+            open_copy_stream(L);
+            TAURUS_HIP(hipStreamWaitEvent(L->copy_stream, L->setup_done, 0));
+            s = L->copy_stream;
+            L->arena.set_stream(s);
+        }
+        scatter_init(L, s, &L->lists);
+        join_setup(L, s);
     } catch (...) {
         L->poisoned = true;
+        if (s != L->s) (void)hipStreamSynchronize(s);
+        L->arena.set_stream(L->s);
         throw;
     }
     L->gather = false;
     L->arena.free_ptr(L->lists.off);
     L->arena.free_ptr(L->lists.src);
-    if (L->gather_ord) L->arena.free_ptr(L->gather_ord);
     L->lists.off = nullptr;
     L->lists.src = nullptr;
-    L->gather_ord = nullptr;
     L->d.weight = L->d.bias = nullptr;
     L->w_host = {};
     L->b_host = {};
@@ -2407,8 +2476,8 @@ static void gather_to_scatter(taurus_layer* L) {
 static const void* stage_host_chunk(taurus_layer* L, const void* x, int64_t rows) {
     const size_t elem = L->d.in_dtype == TAURUS_F32 ? 4 : 2;
     const size_t bytes = (size_t)rows * (size_t)L->d.d_in * elem;
-    if (!L->copy_stream) {
-        TAURUS_HIP(hipStreamCreateWithFlags(&L->copy_stream, hipStreamNonBlocking));
+    open_copy_stream(L);
+    if (!L->stage[1]) {
         // taken on the copy stream, which then waits for a recycled buffer's
         // last user and not for all that the layer's stream has queued
         L->arena.set_stream(L->copy_stream);
@@ -2489,47 +2558,6 @@ static void transform_with_fixup(const ScatterShape& sh, const float* X, int64_t
     fail(TAURUS_E_INVALID, "unsupported row shape G=%d VEC=%d", sh.G, sh.VEC);
 }
 
-static GatherArgs gather_args(const taurus_layer* L) {
-    const taurus_layer_desc& d = L->d;
-    GatherArgs a{};
-    a.X = L->table;
-    a.n = L->n;
-    a.K = d.d_in;
-    a.off = L->lists.off;
-    a.src = L->lists.src;
-    a.W = L->wpack_any;
-    a.NBP = gather_blocks_n(d.d_out);
-    a.bias = L->bias;
-    a.norm = L->n_out;
-    a.out = L->out_dev;
-    a.d_o = d.d_out;
-    a.out_dtype = d.out_dtype;
-    a.relu = d.relu;
-    a.sage = d.agg == TAURUS_SAGE_MEAN ? 1 : 0;
-    a.order = L->gather_ord;
-    a.nonzero = L->lists.nonzero;
-    a.partial = L->partial;
-    a.pairs = d.out_dtype != TAURUS_F32 ? 1 : 0;
-    return a;
-}
-
-// The first push's allocations of a gathered layer; false when the device
-// cannot hold them (the broadcast needs less where inputs are wide or the
-// kernels split).
-static bool gather_alloc(taurus_layer* L, int64_t row) {
-    try {
-        L->table = static_cast<char*>(L->arena.alloc_bytes(L->n * row, "input rows"));
-        const int64_t rows = gather_partial_rows(gather_args(L), L->d.in_dtype);
-        if (rows > 0) L->partial = L->arena.alloc<float>(rows * L->d.d_out, "aggregate products");
-        return true;
-    } catch (const Failure& f) {
-        if (f.status != TAURUS_E_OOM) throw;
-        if (L->table) L->arena.free_ptr(L->table);
-        L->table = nullptr;
-        return false;
-    }
-}
-
 static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int32_t x_on_host) {
     if (L->poisoned) fail(TAURUS_E_STATE, "layer handle is poisoned by an earlier failure");
     if (b < 0 || e > L->n || b >= e || b % L->C != 0 || e != std::min(b + L->C, L->n))
@@ -2544,14 +2572,14 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
         (void)hipGetLastError();
         fail(TAURUS_E_INVALID, "x_on_host = 1 but x is not pinned host memory");
     }
+    hipStream_t s = L->s;
+    if (L->gather && !L->table && (x_on_host || !gather_prepare(L))) gather_to_scatter(L);
     if (L->acc_deferred) {
         L->acc = L->arena.alloc<float>(L->n * (int64_t)L->d_o, "accumulators");
         L->acc_deferred = false;
     }
-    hipStream_t s = L->s;
-    const int64_t row = (int64_t)L->d.d_in * (L->d.in_dtype == TAURUS_F32 ? 4 : 2);
-    if (L->gather && !L->table && (x_on_host || !gather_alloc(L, row))) gather_to_scatter(L);
     if (L->gather) {
+        const int64_t row = (int64_t)L->d.d_in * (L->d.in_dtype == TAURUS_F32 ? 4 : 2);
         if (x_on_host) x = stage_host_chunk(L, x, e - b);
         gather_copy_rows(x, L->table + b * row, (e - b) * row, s);
         if (x_on_host) TAURUS_HIP(hipEventRecord(L->gemm_done[(L->host_pushes - 1) & 1], s));
@@ -2760,7 +2788,8 @@ static int finalize_gather(taurus_layer* L, taurus_stats* st) {
     const bool sage = d.agg == TAURUS_SAGE_MEAN;
     Arena tmp(s);
     uint8_t* ready = nullptr;
-    unsigned long long* dleft = L->list_counts + LIST_COUNTS;
+    unsigned long long* counts = tmp.alloc<unsigned long long>(LIST_COUNTS + 1, "list counts");
+    unsigned long long* dleft = counts + LIST_COUNTS;
     if (!all) {
         uint8_t* pushed = tmp.alloc<uint8_t>(L->nchunks, "pushed chunks");
         ready = tmp.alloc<uint8_t>(L->n, "complete destinations");
@@ -2777,11 +2806,11 @@ static int finalize_gather(taurus_layer* L, taurus_stats* st) {
         L->gathered = true;
     }
     gather_list_counts(L->lists.off, L->lists.src, L->gather_ord, L->gather_ord ? L->lists.nonzero : L->n, L->C,
-                       class_len(NCLASS - 1), PIECE_LEN, L->list_counts, s);
+                       class_len(NCLASS - 1), PIECE_LEN, counts, s);
     unsigned long long c[LIST_COUNTS] = {}, left = 0;
     int bad = 0;
     Readback rb;
-    rb.add(c, L->list_counts, LIST_COUNTS);
+    rb.add(c, counts, LIST_COUNTS);
     rb.add(&bad, L->gather_bad, 1);
     if (!all) rb.add(&left, dleft, 1);
     rb.run(s);
@@ -2805,7 +2834,7 @@ static int finalize_gather(taurus_layer* L, taurus_stats* st) {
         st->short_units = (int64_t)c[LC_SHORT];
         st->wave_units = (int64_t)c[LC_WAVE];
         st->split_segments = (int64_t)c[LC_SPLIT];
-        st->device_bytes = L->arena.peak();
+        st->device_bytes = L->arena.peak() + L->gather_arena.peak();
         st->ms_init = L->ms_init;
         st->ms_index = L->ms_index;
         st->h2d_bytes = L->h2d_bytes;

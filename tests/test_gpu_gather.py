@@ -329,3 +329,59 @@ def test_failed_switch_to_the_broadcast_poisons(torch_cuda, what):
     L.destroy()
     torch.cuda.synchronize()
     assert bool((out == -7.0).all())
+
+
+def test_host_fed_layer_sets_up_the_broadcast_alone(torch_cuda):
+    """Order, norms, weights and table of the gather wait for a first device
+    chunk; a host-fed layer takes none of them, with a set-up stream or not,
+    and both give the same bits."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, chunk = 300_001, 65536
+    g = torch.Generator(device="cuda").manual_seed(4)
+    u, v = (torch.randint(0, n, (900_000,), generator=g, device="cuda") for _ in range(2))
+    key = torch.unique((u * n + v)[u != v])
+    row_off, col_dst = T.build_csr(n, (key // n).int(), (key % n).int())
+    outs = []
+    for setup in (None, torch.cuda.Stream()):
+        for what in ("destination order", "input rows", "source norms"):
+            _fail_alloc(what)
+            L, x, _, _, out = _layer(torch, n, row_off, col_dst, SAGE, 256, 172, BF16, F32, 3, chunk=chunk,
+                                     setup_stream=setup)
+            xh = x.pin_memory()
+            L.push_all(xh)
+            st = L.finalize()
+            _fail_alloc(None)
+            L.destroy()
+            assert st["completed"] == n
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("what", ["input rows", "destination order", "source norms", "packed weights and bias",
+                                  "aggregate products"])
+@pytest.mark.parametrize("setup", [False, True])
+def test_gather_that_does_not_fit_is_broadcast(torch_cuda, what, setup):
+    """Each allocation of the gather refused in turn: the layer is broadcast,
+    with the broadcast's bits (a profiled layer's)."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, chunk = 300_001, 65536
+    g = torch.Generator(device="cuda").manual_seed(4)
+    u, v = (torch.randint(0, n, (900_000,), generator=g, device="cuda") for _ in range(2))
+    key = torch.unique((u * n + v)[u != v])
+    row_off, col_dst = T.build_csr(n, (key // n).int(), (key % n).int())
+    agg, d_in, d_out = (GCN, 64, 32) if what == "source norms" else (SAGE, 256, 172)
+    outs = []
+    for profile in (1, 0):
+        L, x, _, _, out = _layer(torch, n, row_off, col_dst, agg, d_in, d_out, BF16, F32, 3, chunk=chunk,
+                                 profile=profile, setup_stream=torch.cuda.Stream() if setup else None)
+        if not profile:
+            _fail_alloc(what)
+        L.push_all(x.cuda())
+        st = L.finalize()
+        _fail_alloc(None)
+        L.destroy()
+        assert st["completed"] == n
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
