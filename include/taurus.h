@@ -422,10 +422,14 @@ void taurus_plan_destroy(taurus_plan* plan);
  * bf16 inputs of at most 256 columns whose rows take at most 8 * d_out
  * bytes, and a sample that leaves out some edge, is aggregated by
  * destination instead: it keeps the sample as in-edge lists, its pushes copy
- * x into a table of all rows (allocated by the first push), and
- * taurus_finalize evaluates every destination whose messages have all been
- * pushed.  If its first chunk comes from the host, or the device cannot hold
- * the table, it is broadcast like the others.  *out receives the handle.  Blocks until the index is built.
+ * x into a table of all rows, and the push of the last chunk evaluates every
+ * destination (with chunks missing, taurus_finalize evaluates those whose
+ * messages have all been pushed).  If its first chunk comes from the host, or
+ * the device cannot hold the table, it is broadcast like the others.  Which
+ * of the two is known, and their memory taken, at the first push: that push
+ * may block, and may return TAURUS_E_OOM (the handle is then poisoned).
+ * *out receives the handle.  Blocks until the index is built or the sample
+ * drawn.
  * Errors: TAURUS_E_INVALID for bad arguments or a graph that is not a valid
  * simple CSR; TAURUS_E_BUDGET when the budget cannot hold the layer;
  * TAURUS_E_OOM / TAURUS_E_DEVICE from the runtime.  On error *out is NULL.
@@ -447,7 +451,8 @@ int taurus_layer_init(const taurus_graph* g, const taurus_layer_desc* d, taurus_
  * compute; Sec. 3.3).  x must stay valid and unchanged until the next call
  * on this handle returns.  Chunks may be pushed in any order;
  * each exactly once (a repeat returns TAURUS_E_STATE).  Asynchronous on the
- * layer's stream.
+ * layer's stream, on which every output row is written once the work of the
+ * last chunk's push is done.
  */
 int taurus_push_chunk(taurus_layer* L, int64_t src_begin, int64_t src_end, const void* x,
                       int32_t x_on_host);
@@ -456,7 +461,8 @@ int taurus_push_chunk(taurus_layer* L, int64_t src_begin, int64_t src_end, const
  * Wait for the layer's work, check that every destination completed (Sec.
  * 3.6: a vertex graduates once its pending count reaches zero, its output
  * row written by the flush that completes it; a layer aggregated by
- * destination writes its rows here) and fill *stats (may be NULL).  Returns TAURUS_E_INCOMPLETE (with the count in
+ * destination that lacks chunks writes its complete rows here) and fill
+ * *stats (may be NULL).  Returns TAURUS_E_INCOMPLETE (with the count in
  * stats->pending_left) if some destination still has pending messages, e.g.
  * because a chunk was never pushed.  After TAURUS_OK every row of desc.out
  * holds its final value.

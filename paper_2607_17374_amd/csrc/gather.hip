@@ -5,7 +5,8 @@
 // of at most a few dozen in-edges over many chunks nearly every message is a
 // segment of its own.  A layer whose chunks all stay in device memory does
 // not need the accumulators: the pushes copy the source rows into a table
-// of the layer's own, and finalize evaluates
+// of the layer's own, and the last push (or a finalize with chunks missing,
+// for the rows that are complete) evaluates
 //     out[v] = act(phi_v * ((sum_{u in M(v)} w_u x_u) W) + b)
 // in one kernel, by linearity the same value (the aggregate is formed
 // before the linear map instead of after, Sec. 3.9), from the kept in-edge

@@ -2276,8 +2276,8 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
     }
 }
 
-// Whether a layer is aggregated by destination at finalize (gather.hip)
-// instead of broadcast chunk by chunk: sampled layers in core, whose kept
+// Whether a layer is aggregated by destination once its chunks are there
+// (gather.hip) instead of broadcast chunk by chunk: sampled layers in core, whose kept
 // lists are short, when a message's input row is less to read than the
 // accumulator row it would read and write (both 4 d_out bytes) and the table
 // of input rows takes at most twice the accumulators' memory, which is the
@@ -2558,6 +2558,14 @@ static void transform_with_fixup(const ScatterShape& sh, const float* X, int64_t
     fail(TAURUS_E_INVALID, "unsupported row shape G=%d VEC=%d", sh.G, sh.VEC);
 }
 
+// A gathered layer's rows (ready: those it names) from the table.
+static void run_gather(taurus_layer* L, const uint8_t* ready) {
+    GatherArgs a = gather_args(L);
+    a.ready = ready;
+    gather_layer(a, L->d.in_dtype, L->s);
+    L->gathered = true;
+}
+
 static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int32_t x_on_host) {
     if (L->poisoned) fail(TAURUS_E_STATE, "layer handle is poisoned by an earlier failure");
     if (b < 0 || e > L->n || b >= e || b % L->C != 0 || e != std::min(b + L->C, L->n))
@@ -2586,6 +2594,9 @@ static void push_chunk(taurus_layer* L, int64_t b, int64_t e, const void* x, int
         L->pushed[(size_t)k] = 1;
         L->npushed++;
         L->gathered = false;
+        // the last chunk completes every row, as a broadcast's does: what
+        // follows on the stream may read them without a finalize between
+        if (L->npushed == L->nchunks) run_gather(L, nullptr);
         return;
     }
     const ChunkIndex& idx = *L->idx;
@@ -2779,8 +2790,8 @@ static void run_gat_passes(taurus_layer* L) {
     L->gat_done = true;
 }
 
-// A gathered layer: aggregate (the destinations whose messages have all been
-// pushed), and the statistics from the lists.
+// A gathered layer: with chunks missing, aggregate the destinations whose
+// messages have all been pushed; the statistics from the lists.
 static int finalize_gather(taurus_layer* L, taurus_stats* st) {
     hipStream_t s = L->s;
     const taurus_layer_desc& d = L->d;
@@ -2799,12 +2810,7 @@ static int finalize_gather(taurus_layer* L, taurus_stats* st) {
         pinned_staging_in_flight(s);
         gather_ready(L->lists.off, L->lists.src, L->n, L->C, pushed, ready, dleft, s);
     }
-    if (L->table && !L->gathered) {
-        GatherArgs a = gather_args(L);
-        a.ready = ready;
-        gather_layer(a, d.in_dtype, s);
-        L->gathered = true;
-    }
+    if (L->table && !L->gathered) run_gather(L, ready);
     gather_list_counts(L->lists.off, L->lists.src, L->gather_ord, L->gather_ord ? L->lists.nonzero : L->n, L->C,
                        class_len(NCLASS - 1), PIECE_LEN, counts, s);
     unsigned long long c[LIST_COUNTS] = {}, left = 0;

@@ -1,4 +1,4 @@
-"""Sampled layers kept in core (aggregated by destination at finalize) against
+"""Sampled layers kept in core (aggregated by destination) against
 a 64-bit evaluation of the edges the layer says it keeps: widths at the edges
 of the k-blocks and column groups, every family and type, lists of 0 to k
 in-edges, partial pushes, host-fed chunks, values that are not finite.
@@ -385,3 +385,31 @@ def test_gather_that_does_not_fit_is_broadcast(torch_cuda, what, setup):
         assert st["completed"] == n
         outs.append(out)
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("n", [1025, 300_001])
+def test_rows_are_written_by_the_last_push(torch_cuda, n):
+    """Every row is there, in stream order, after the last push: the next
+    layer reads them before this one is finalized."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    g = torch.Generator(device="cuda").manual_seed(6)
+    u, v = (torch.randint(0, n, (5 * n,), generator=g, device="cuda") for _ in range(2))
+    key = torch.unique((u * n + v)[u != v])
+    row_off, col_dst = T.build_csr(n, (key // n).int(), (key % n).int())
+    got = []
+    for early in (False, True):
+        A, x, _, _, h = _layer(torch, n, row_off, col_dst, SAGE, 32, 64, BF16, BF16, 3, chunk=65536)
+        B, _, _, _, out = _layer(torch, n, row_off, col_dst, GCN, 64, 16, BF16, F32, 4, chunk=65536)
+        A.push_all(x.cuda())
+        if not early:
+            A.finalize()
+        B.push_all(h)
+        torch.cuda.synchronize()
+        got.append((h.clone(), out.clone()))
+        for L in (A, B):
+            assert L.finalize()["completed"] == n
+            L.destroy()
+        assert torch.equal(h, got[-1][0]) and torch.equal(out, got[-1][1])
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert not bool((got[1][1] == -7.0).any())
