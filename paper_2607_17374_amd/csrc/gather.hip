@@ -634,32 +634,46 @@ void gather_layer(const GatherArgs& g, int dtype, hipStream_t s) {
 
 int gather_blocks_n(int d_o) { return (int)ceil_div(d_o, 64) * 4; }
 
+static uint32_t bits_of(uint16_t x) { return x; }
+static uint32_t bits_of(float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    return u;
+}
+
 // Fragments of a row-major W (row stride ld) [K][d_o] after those already in
 // packed: block (kb, nb) holds, for lane (i, lk), the EP consecutive k at
 // kb*KBLK + EP*lk of column 16*nb + i, or with pairs (16-bit outputs, so that
 // a lane's columns of two blocks make one 16-byte store) column
-// 32*(nb/2) + 8*(i/4) + 4*(nb%2) + i%4; zeros past K and d_o.
+// 32*(nb/2) + 8*(i/4) + 4*(nb%2) + i%4; zeros past K and d_o.  True when every
+// packed value is finite (exp: the type's exponent bits).
 template <class T, class Cvt>
-static void pack(const float* W, int ld, int K, int d_o, bool pairs, int ep, Cvt cvt, std::vector<T>& packed) {
+static bool pack(const float* W, int ld, int K, int d_o, bool pairs, int ep, uint32_t exp, Cvt cvt,
+                 std::vector<T>& packed) {
     const int kbn = (int)ceil_div(K, 4 * ep), nbp = gather_blocks_n(d_o);
     const size_t base = packed.size();
     packed.resize(base + (size_t)kbn * nbp * 64 * ep, T(0));
     T* p = packed.data() + base;
+    bool finite = true;
     for (int kb = 0; kb < kbn; kb++)
         for (int nb = 0; nb < nbp; nb++)
             for (int l = 0; l < 64; l++, p += ep) {
                 const int i = l & 15, k0 = kb * 4 * ep + ep * (l >> 4);
                 const int col = pairs ? 32 * (nb >> 1) + 8 * (i >> 2) + 4 * (nb & 1) + (i & 3) : 16 * nb + i;
                 if (col >= d_o) continue;
-                for (int c = 0; c < ep && k0 + c < K; c++) p[c] = cvt(W[(size_t)(k0 + c) * ld + col]);
+                for (int c = 0; c < ep && k0 + c < K; c++) {
+                    p[c] = cvt(W[(size_t)(k0 + c) * ld + col]);
+                    finite &= (bits_of(p[c]) & exp) != exp;
+                }
             }
+    return finite;
 }
 
-void gather_pack_f32(const float* W, int ld, int K, int d_o, bool pairs, std::vector<float>& packed) {
-    pack(W, ld, K, d_o, pairs, 4, [](float x) { return x; }, packed);
+bool gather_pack_f32(const float* W, int ld, int K, int d_o, bool pairs, std::vector<float>& packed) {
+    return pack(W, ld, K, d_o, pairs, 4, 0x7f800000u, [](float x) { return x; }, packed);
 }
-void gather_pack_bf16(const float* W, int ld, int K, int d_o, bool pairs, std::vector<uint16_t>& packed) {
-    pack(W, ld, K, d_o, pairs, 8, [](float x) { return host_f32_to_bf16(x); }, packed);
+bool gather_pack_bf16(const float* W, int ld, int K, int d_o, bool pairs, std::vector<uint16_t>& packed) {
+    return pack(W, ld, K, d_o, pairs, 8, 0x7f80u, [](float x) { return host_f32_to_bf16(x); }, packed);
 }
 
 // -------------------------------------------------------------- row table --

@@ -28,9 +28,10 @@ struct GatherArgs {
 };
 
 uint16_t host_f32_to_bf16(float f);   // round to nearest even (gemm.hip)
-// host weights [K][d_o] (row stride ld) appended as matrix-core fragments
-void gather_pack_f32(const float* W, int ld, int K, int d_o, bool pairs, std::vector<float>& packed);
-void gather_pack_bf16(const float* W, int ld, int K, int d_o, bool pairs, std::vector<uint16_t>& packed);
+// host weights [K][d_o] (row stride ld) appended as matrix-core fragments;
+// false when one is not finite in the packed type
+bool gather_pack_f32(const float* W, int ld, int K, int d_o, bool pairs, std::vector<float>& packed);
+bool gather_pack_bf16(const float* W, int ld, int K, int d_o, bool pairs, std::vector<uint16_t>& packed);
 int gather_blocks_n(int d_o);
 // rows of g.partial the layer needs (0: none), from every other member
 int64_t gather_partial_rows(const GatherArgs& g, int dtype);

@@ -2354,7 +2354,9 @@ static GatherArgs gather_args(const taurus_layer* L) {
 // host chunk, which broadcasts the layer, then costs what it would have cost
 // without the gather): table, order, norms, packed weights, partial products.
 // False, holding nothing, when the device cannot hold them (the broadcast
-// needs less where inputs are wide or the kernels split).
+// needs less where inputs are wide or the kernels split), and when a weight is
+// not finite: its products with the parts or sums of an aggregate are not
+// what its products with the inputs add up to.
 static bool gather_prepare(taurus_layer* L) {
     const taurus_layer_desc& d = L->d;
     const int64_t n = L->n, row = (int64_t)d.d_in * (d.in_dtype == TAURUS_F32 ? 4 : 2);
@@ -2362,6 +2364,17 @@ static bool gather_prepare(taurus_layer* L) {
     Arena& arena = L->gather_arena;
     arena.set_stream(s);
     try {
+        // weights: the aggregate's columns, then GraphSAGE's self columns
+        const float* w = L->w_host.data();
+        std::vector<float> p32;
+        std::vector<uint16_t> p16;
+        const bool pairs = d.out_dtype != TAURUS_F32;
+        for (int h = 0; h < (d.agg == TAURUS_SAGE_MEAN ? 2 : 1); h++) {
+            const bool finite =
+                d.in_dtype == TAURUS_F32 ? gather_pack_f32(w + h * d.d_out, L->ncols, d.d_in, d.d_out, pairs, p32)
+                                         : gather_pack_bf16(w + h * d.d_out, L->ncols, d.d_in, d.d_out, pairs, p16);
+            if (!finite) return false;
+        }
         L->table = static_cast<char*>(arena.alloc_bytes(n * row, "input rows"));
         if (n >= GATHER_ORDER_MIN) {
             Arena tmp(s);
@@ -2370,15 +2383,6 @@ static bool gather_prepare(taurus_layer* L) {
         if (d.agg == TAURUS_GCN_SYM) {
             L->n_out = arena.alloc<float>(n, "source norms");
             gather_norms(L->lists.src, L->lists.kept, n, L->n_out, s);
-        }
-        // weights: the aggregate's columns, then GraphSAGE's self columns
-        const float* w = L->w_host.data();
-        std::vector<float> p32;
-        std::vector<uint16_t> p16;
-        const bool pairs = d.out_dtype != TAURUS_F32;
-        for (int h = 0; h < (d.agg == TAURUS_SAGE_MEAN ? 2 : 1); h++) {
-            if (d.in_dtype == TAURUS_F32) gather_pack_f32(w + h * d.d_out, L->ncols, d.d_in, d.d_out, pairs, p32);
-            else gather_pack_bf16(w + h * d.d_out, L->ncols, d.d_in, d.d_out, pairs, p16);
         }
         const size_t wbytes = p32.size() * 4 + p16.size() * 2;  // whole fragments: a multiple of 1 KiB
         const size_t pbytes = wbytes + (size_t)d.d_out * 4;

@@ -413,3 +413,38 @@ def test_rows_are_written_by_the_last_push(torch_cuda, n):
         assert torch.equal(h, got[-1][0]) and torch.equal(out, got[-1][1])
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
     assert not bool((got[1][1] == -7.0).any())
+
+
+@pytest.mark.parametrize("dt", [F32, BF16])
+@pytest.mark.parametrize("agg", [SAGE, GCN, GIN])
+def test_weights_that_are_not_finite(torch_cuda, agg, dt):
+    """An infinite weight (in bf16 also a finite fp32 one past its range), and
+    a NaN, give what the broadcast gives, bit for bit: the layer is broadcast."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n = 1000
+    src, dst, row_off, col_dst = _graph(torch, n, 4000, 5)
+    rng = np.random.default_rng(1)
+    x = torch.from_numpy(rng.standard_normal((n, 64)).astype(np.float32)).cuda()
+    x = x.bfloat16() if dt else x
+    x[11] = 0
+    for bad in (np.inf, np.nan, 3.4e38):
+        W = (rng.standard_normal((64, 32 if agg == SAGE else 16)) / 8).astype(np.float32)
+        W[5, 3] = bad
+        got = []
+        for profile in (1, 0):
+            out = torch.full((n, 16), -7.0, device="cuda")
+            L = T.Layer(n, row_off, col_dst, agg=agg, d_in=64, d_out=16, weight_cat=W, bias=None, out=out,
+                        in_dtype=dt, fanout=4, layer=1, seed=3, chunk=192, profile=profile)
+            L.push_all(x)
+            L.finalize()
+            L.destroy()
+            got.append(out)
+        if bad == 3.4e38 and dt == F32:          # finite there: the same up to rounding where it does not overflow
+            a, b = got[0].double(), got[1].double()
+            ok = torch.isfinite(a) & torch.isfinite(b)
+            assert ok.float().mean() > 0.5 and torch.allclose(a[ok], b[ok], rtol=1e-4, atol=1e-5)
+        else:
+            assert torch.equal(got[0].isnan(), got[1].isnan())
+            assert torch.equal(got[0].nan_to_num(7.0), got[1].nan_to_num(7.0))
+            assert bool(got[0].isinf().any() | got[0].isnan().any())
