@@ -138,7 +138,10 @@ struct GatherTile {
         return __builtin_amdgcn_readfirstlane(d);
     }
     // agg = the destination's weighted sum (GraphSAGE: its mean; otherwise
-    // with the vertex's own message)
+    // with the vertex's own message).  Rows are added at g.scale, a power of
+    // two no larger than one over the longest list and the vertex itself, so
+    // that a sum of large inputs does not overflow before the linear map; the
+    // mean, or the output (store), takes it out again, exactly.
     static __device__ inline void aggregate(const GatherArgs& g, const Dest& t, int dmax, int lk, uint32_t (&id)[U],
                                             float (&agg)[KB][EP]) {
         const bool partial = g.K != KB * KBLK;  // some lanes' pieces lie past the row
@@ -152,7 +155,7 @@ struct GatherTile {
 #pragma unroll
             for (int j = 0; j < U; j++) {
                 if (at + j < t.d) {
-                    w[j] = g.norm ? g.norm[id[j]] : 1.0f;
+                    w[j] = g.norm ? g.norm[id[j]] : g.scale;
 #pragma unroll
                     for (int kb = 0; kb < KB; kb++)
                         if (!partial || kb * KBLK + EP * lk < g.K) r[j][kb] = piece(g, id[j], kb, lk);
@@ -172,13 +175,13 @@ struct GatherTile {
             for (int j = 0; j < U; j++) id[j] = nid[j];
         }
         if (g.sage) {
-            const float sig = t.d > 0 ? 1.0f / (float)t.d : 0.0f;
+            const float sig = t.d > 0 ? g.unscale / (float)t.d : 0.0f;
 #pragma unroll
             for (int kb = 0; kb < KB; kb++)
 #pragma unroll
                 for (int i = 0; i < EP; i++) agg[kb][i] *= sig;
         } else if (t.live) {
-            const float w = g.norm ? g.norm[t.v] : 1.0f;
+            const float w = g.norm ? g.norm[t.v] : g.scale;
 #pragma unroll
             for (int kb = 0; kb < KB; kb++)
                 if (!partial || kb * KBLK + EP * lk < g.K) Op::add(w, piece(g, t.v, kb, lk), agg[kb]);
@@ -258,7 +261,8 @@ struct GatherTile {
     static __device__ inline void store(const GatherArgs& g, const float* bias, const Dest& t, int nb0, int lk,
                                         Sums sums) {
         if (!t.live) return;
-        const float phi = g.norm ? 1.0f / sqrtf((float)(t.d + 1)) : 1.0f;
+        const float out_scale = g.sage ? 1.0f : g.unscale;
+        const float phi = g.norm ? out_scale / sqrtf((float)(t.d + 1)) : out_scale;
         auto value = [&](int j) {
             const int c = col(g, nb0 + j, lk);
             const floatx4 x = sums(j);
@@ -734,18 +738,18 @@ __global__ void k_source_counts(const uint32_t* __restrict__ src, int64_t kept, 
     if (i < kept) atomicAdd(&deg[src[i]], 1);
 }
 // counts become norms in place
-__global__ void k_source_norms(int64_t n, float* __restrict__ norm) {
+__global__ void k_source_norms(int64_t n, float scale, float* __restrict__ norm) {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < n) norm[u] = 1.0f / sqrtf((float)(__float_as_int(norm[u]) + 1));
+    if (u < n) norm[u] = scale / sqrtf((float)(__float_as_int(norm[u]) + 1));
 }
 
-void gather_norms(const uint32_t* src, int64_t kept, int64_t n, float* norm, hipStream_t s) {
+void gather_norms(const uint32_t* src, int64_t kept, int64_t n, float scale, float* norm, hipStream_t s) {
     fill_i32(reinterpret_cast<int32_t*>(norm), n, 0, s);
     if (kept > 0) {
         k_source_counts<<<(unsigned)ceil_div(kept, 256), 256, 0, s>>>(src, kept, reinterpret_cast<int32_t*>(norm));
         TAURUS_CHECK_LAUNCH();
     }
-    k_source_norms<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(n, norm);
+    k_source_norms<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(n, scale, norm);
     TAURUS_CHECK_LAUNCH();
 }
 

@@ -17,7 +17,8 @@ struct GatherArgs {
     const void* W;          // packed weights: the aggregate's, then (sage) the self half's
     int NBP;                // 16-column blocks per k-block of W
     const float* bias;      // [d_o]
-    const float* norm;      // GCN: d^_out(u)^-1/2 of the sampled graph, else null
+    const float* norm;      // GCN: d^_out(u)^-1/2 of the sampled graph, times scale, else null
+    float scale, unscale;   // messages are summed at scale (GatherTile::aggregate); 1 / scale
     void* out;              // [n][d_o]
     int d_o, out_dtype, relu, sage;
     const uint8_t* ready;   // null: every destination
@@ -42,8 +43,8 @@ void gather_copy_rows(const void* x, void* table, int64_t bytes, hipStream_t s);
 constexpr int64_t GATHER_ORDER_MIN = 1 << 18;
 uint32_t* gather_order(const int64_t* off, int64_t n, int k, Arena& arena, Arena& tmp, int* bad, int bad_bit,
                        hipStream_t s);
-// norm[u] = (in-edges of the lists with source u + 1)^-1/2
-void gather_norms(const uint32_t* src, int64_t kept, int64_t n, float* norm, hipStream_t s);
+// norm[u] = scale * (in-edges of the lists with source u + 1)^-1/2
+void gather_norms(const uint32_t* src, int64_t kept, int64_t n, float scale, float* norm, hipStream_t s);
 
 enum { LC_SEGMENTS, LC_OWN, LC_SHORT, LC_WAVE, LC_SPLIT, LIST_COUNTS };
 void gather_list_counts(const int64_t* off, const uint32_t* src, const uint32_t* order, int64_t n, int64_t C,

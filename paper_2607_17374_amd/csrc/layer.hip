@@ -2338,6 +2338,8 @@ static GatherArgs gather_args(const taurus_layer* L) {
     a.NBP = gather_blocks_n(d.d_out);
     a.bias = L->bias;
     a.norm = L->n_out;
+    a.scale = std::ldexp(1.0f, -bits_for(d.fanout));   // at most fanout rows and the vertex's own: 2^bits > fanout
+    a.unscale = 1.0f / a.scale;
     a.out = L->out_dev;
     a.d_o = d.d_out;
     a.out_dtype = d.out_dtype;
@@ -2382,7 +2384,7 @@ static bool gather_prepare(taurus_layer* L) {
         }
         if (d.agg == TAURUS_GCN_SYM) {
             L->n_out = arena.alloc<float>(n, "source norms");
-            gather_norms(L->lists.src, L->lists.kept, n, L->n_out, s);
+            gather_norms(L->lists.src, L->lists.kept, n, gather_args(L).scale, L->n_out, s);
         }
         const size_t wbytes = p32.size() * 4 + p16.size() * 2;  // whole fragments: a multiple of 1 KiB
         const size_t pbytes = wbytes + (size_t)d.d_out * 4;

@@ -448,3 +448,22 @@ def test_weights_that_are_not_finite(torch_cuda, agg, dt):
             assert torch.equal(got[0].isnan(), got[1].isnan())
             assert torch.equal(got[0].nan_to_num(7.0), got[1].nan_to_num(7.0))
             assert bool(got[0].isinf().any() | got[0].isnan().any())
+
+
+@pytest.mark.parametrize("n", [1000, 270_001])
+@pytest.mark.parametrize("dt", [F32, BF16])
+@pytest.mark.parametrize("agg", [SAGE, GCN, GIN])
+def test_sums_past_the_type_before_the_linear_map(torch_cuda, agg, dt, n):
+    """Inputs whose sum over a list exceeds fp32 while the outputs do not."""
+    torch = torch_cuda
+    src, dst, row_off, col_dst = _graph(torch, n, 6 * n, 5)
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, 256, 16, dt, F32, 6, chunk=65536)
+    xd = x.cuda()
+    xd[:, 9] = 1e38
+    L.push_all(xd)
+    L.finalize()
+    words, _ = L.sampled_edges()
+    L.destroy()
+    z = _reference(agg, n, src, dst, words, xd.double().cpu().numpy(), W, b, True, 16)
+    assert np.abs(z).max() > 1e36
+    _check(out, z, F32)
