@@ -467,3 +467,24 @@ def test_sums_past_the_type_before_the_linear_map(torch_cuda, agg, dt, n):
     z = _reference(agg, n, src, dst, words, xd.double().cpu().numpy(), W, b, True, 16)
     assert np.abs(z).max() > 1e36
     _check(out, z, F32)
+
+
+@pytest.mark.parametrize("n,hubs", [(1000, 1), (5000, 3), (4097, 4097)])
+def test_gcn_norms_of_hub_sources(torch_cuda, n, hubs):
+    """Sampled GCN where some sources are in every list, or every source is
+    in few: the norms count each kept out-edge once (tiles of 4,096 entries,
+    a source's two table slots taken or not)."""
+    torch = torch_cuda
+    import paper_2607_17374_amd as T
+    rng = np.random.default_rng(n)
+    u = np.concatenate([rng.integers(0, n, 8 * n)] + [np.full(n, h) for h in range(hubs if hubs < 10 else 0)])
+    v = np.concatenate([rng.integers(0, n, 8 * n)] + [np.arange(n)] * (hubs if hubs < 10 else 0))
+    key = np.unique((u * n + v)[u != v])
+    src, dst = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    row_off, col_dst = T.build_csr(n, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda())
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, GCN, 64, 32, F32, F32, 7, chunk=1024, relu=False)
+    L.push_all(x.cuda())
+    L.finalize()
+    words, _ = L.sampled_edges()
+    L.destroy()
+    _check(out, _reference(GCN, n, src, dst, words, x.double().numpy(), W, b, False, 32), F32)
