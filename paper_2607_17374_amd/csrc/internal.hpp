@@ -215,20 +215,27 @@ void sample_mask(const taurus_graph& g, const Csc& csc, uint64_t seed, int layer
 // chunk of v's smallest kept source (left as it was when none is kept).
 // Returns the number kept.  Sets bit 32 of *bad (device) for an in-list
 // the pass could not settle (repeated sources).
+// known (optional): the number kept and their offsets, from sample_shape.
+struct SampleLists;
 int64_t sample_items(const Csc& csc, int64_t n, uint64_t seed, int layer, int k, int64_t C, int vbits,
-                     Arena& key_arena, Arena& val_arena, SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad,
-                     hipStream_t s);
-// The same sample as lists: off[v] .. off[v + 1] of src, sources ascending
-// (both from arena, the temporaries from tmp).  False, with nothing drawn or
-// held, when the sample is all e in-edges.
+                     const SampleLists* known, Arena& key_arena, Arena& val_arena, SortBuffers& sb, int32_t* m,
+                     int32_t* first_chunk, int* bad, hipStream_t s);
+// The same sample as lists: off[v] .. off[v + 1] of src, sources ascending.
 struct SampleLists {
     int64_t* off = nullptr;   // [n + 1]
-    uint32_t* src = nullptr;  // [kept]
+    uint32_t* src = nullptr;  // [kept]; null until drawn
     int64_t kept = 0;
     int64_t nonzero = 0;      // destinations with at least one
+    int64_t segments = 0;     // sum of min(list length, chunks): the most (destination, chunk) segments
+    int64_t rounds = 0;       // sum of the longest list of every 16 consecutive destinations
+    int64_t longest = 0;
 };
-bool sample_lists(const Csc& csc, int64_t n, int64_t e, uint64_t seed, int layer, int k, Arena& arena, Arena& tmp,
-                  SampleLists& out, int* bad, hipStream_t s);
+// off and the counts, which follow from the degrees (blocks), then the draw;
+// both from arena, the temporaries from tmp
+void sample_shape(const Csc& csc, int64_t n, int k, int64_t nchunks, Arena& arena, Arena& tmp, SampleLists& out,
+                  hipStream_t s);
+void sample_lists(const Csc& csc, int64_t n, uint64_t seed, int layer, int k, Arena& arena, Arena& tmp,
+                  SampleLists& l, int* bad, hipStream_t s);
 // sample_items' output from those lists
 int64_t list_items(const SampleLists& l, int64_t n, int64_t C, int vbits, Arena& key_arena, Arena& val_arena,
                    SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad, hipStream_t s);

@@ -1420,7 +1420,7 @@ static double ms_since(std::chrono::steady_clock::time_point t0) {
 
 // A sampled layer's index (sample != null) takes its items straight from the
 // fanout sampler; an exact layer's from every CSR edge.
-// (from lists already drawn, when given).
+// (lists: drawn already, or their offsets alone, or null).
 struct SampleReq {
     const Csc* csc;
     uint64_t seed;
@@ -1493,11 +1493,11 @@ static std::shared_ptr<ChunkIndex> build_index(const taurus_graph& g, int64_t C,
         // the sampler's kept in-edges come destination-major with sources
         // ascending, so a stable sort by the chunk field alone orders them
         // by (chunk, destination, source)
-        if (sample->lists)
+        if (sample->lists && sample->lists->src)
             items = list_items(*sample->lists, n, C, vbits, tmp, idx->arena, sb, idx->m, first_chunk, bad, s);
         else
-            items = sample_items(*sample->csc, n, sample->seed, sample->layer, sample->k, C, vbits, tmp, idx->arena,
-                                 sb, idx->m, first_chunk, bad, s);
+            items = sample_items(*sample->csc, n, sample->seed, sample->layer, sample->k, C, vbits, sample->lists, tmp,
+                                 idx->arena, sb, idx->m, first_chunk, bad, s);
         radix_sort_u64(sb, items, cbits, tmp, s, bad, 8, nullptr, kshift);
     } else {
         sb.keys[0] = tmp.alloc<uint64_t>(e, "index keys");
@@ -2067,7 +2067,7 @@ static void check_chunk_bytes(const taurus_layer* L) {
 
 // Set-up of a layer that broadcasts its chunks: chunk index, counts,
 // weights, accumulators.  lists: the kept in-edges of a sampled layer that
-// drew them already.
+// drew them already, or their offsets.
 static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* lists) {
     const taurus_graph& g = L->g;
     const taurus_layer_desc& d = L->d;
@@ -2296,22 +2296,47 @@ static bool gather_rule(const taurus_layer_desc& d) {
            d.d_in <= GATHER_MAX_K && in_bytes <= 8 * (int64_t)d.d_out;
 }
 
+// Whether this sample's gather costs less than its broadcast, in bytes of
+// cached rows read at their rate (about 7.5 TB/s).  Gather: each message's
+// input row and, as issue and latency, 512 bytes more, for as many messages as
+// the waves' rounds hold (16 destinations take as many as their longest list;
+// ordered by length they take their own); or, where that is more, the longest
+// list's rows one after the other, 1.7 us for each 256 bytes.  Broadcast: each
+// message's transformed row and 384 bytes of index, each segment's
+// accumulator row in and out, and 2 GB for the index's launches and
+// synchronisations (GCN, whose norms draw the sample again: 1,000 bytes a
+// message and 10 MB an entry of the longest list more).  Measured over 150
+// samples of 20K to 1M vertices (4 to 400 in-edges, fanouts 1 to 512, rows of 128 to
+// 1,024 bytes in and 64 to 1,024 out), broadcast / gather time: lists of at
+// most 64 mostly 1.05 to 2.5; 200K vertices, 100 in-edges, fanout 256,
+// 256 -> 128 fp32 2.87 / 6.41 ms, 128 -> 128 bf16 2.79 / 4.08; 400K, the same,
+// 5.32 / 6.75 and 5.12 / 4.81; 1M vertices, 4 in-edges, hubs of 512 and more,
+// fanout 512, 64 -> 64 fp32 2.22 / 2.80.
+static bool gather_pays(const taurus_layer* L) {
+    const taurus_layer_desc& d = L->d;
+    const SampleLists& l = L->lists;
+    const int64_t in = (int64_t)d.d_in * (d.in_dtype == TAURUS_F32 ? 4 : 2), out = (int64_t)d.d_out * 4;
+    const int64_t held = L->n >= GATHER_ORDER_MIN ? l.kept : 16 * l.rounds;
+    return std::max(held * (in + 512), l.longest * in * 50000) <=
+           l.kept * (out + 384) + 2 * l.segments * out + 2000000000 +
+               (d.agg == TAURUS_GCN_SYM ? l.kept * 1000 + l.longest * 10000000 : 0);
+}
+
 // The sample, and a copy of what either form needs later.  False (nothing set
-// up but the in-edge lists) when the sample keeps every edge: such a layer is
-// the exact layer, and is broadcast like it so that the two agree bit for bit.
+// up but the in-edge lists and the sample's offsets) when the layer is better
+// broadcast, or the sample keeps every edge: such a layer is the exact layer,
+// and is broadcast like it so that the two agree bit for bit.
 static bool gather_init(taurus_layer* L, hipStream_t s) {
     const taurus_layer_desc& d = L->d;
     const auto t_index = std::chrono::steady_clock::now();
     L->csc = layer_csc(L, s, nullptr);
     {
         Arena tmp(s);
-        int* bad = L->arena.alloc<int>(1, "sampler flag");
-        fill_i32(bad, 1, 0, s);
-        if (!sample_lists(*L->csc, L->n, L->g.e, d.seed, d.layer, d.fanout, L->arena, tmp, L->lists, bad, s)) {
-            L->arena.free_ptr(bad);
-            return false;
-        }
-        L->gather_bad = bad;
+        sample_shape(*L->csc, L->n, d.fanout, L->nchunks, L->arena, tmp, L->lists, s);
+        if (L->lists.kept == L->g.e || !gather_pays(L)) return false;
+        L->gather_bad = L->arena.alloc<int>(1, "sampler flag");
+        fill_i32(L->gather_bad, 1, 0, s);
+        sample_lists(*L->csc, L->n, d.seed, d.layer, d.fanout, L->arena, tmp, L->lists, L->gather_bad, s);
     }
     L->gather = true;
     L->ms_index = ms_since(t_index);
@@ -2428,7 +2453,11 @@ static void layer_init(taurus_layer* L) {
     // refuses as an argument is refused here
     const bool gather = gather_rule(L->d);
     if (gather) check_chunk_bytes(L);
-    if (!gather || !gather_init(L, s)) scatter_init(L, s, nullptr);
+    if (!gather || !gather_init(L, s)) {
+        scatter_init(L, s, gather ? &L->lists : nullptr);
+        if (L->lists.off) L->arena.free_ptr(L->lists.off);
+        L->lists.off = nullptr;
+    }
     join_setup(L, s);
     L->ms_init = ms_since(t_start);  // host time; the work stays queued on the stream
 }

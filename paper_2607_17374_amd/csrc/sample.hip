@@ -594,48 +594,84 @@ static void sample_pass(const Csc& csc, int64_t n, uint64_t seed, int layer, int
     }
 }
 
-// kept per destination, min(d_in(v), k), and the number of destinations
-// that keep any (nonzero, may be null: one atomic per workgroup of a bounded
-// grid)
-__global__ __launch_bounds__(256) void k_sample_counts(const int64_t* __restrict__ in_off, int64_t n, int k,
-                                                       int32_t* __restrict__ m,
-                                                       unsigned long long* __restrict__ nonzero) {
-    __shared__ unsigned int part[4];
-    unsigned int c = 0;
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
-        const int x = (int)min(in_off[v + 1] - in_off[v], (int64_t)k);
-        m[v] = x;
-        c += x > 0;
-    }
-    if (!nonzero) return;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(nonzero, (unsigned long long)(part[0] + part[1] + part[2] + part[3]));
-}
-static unsigned count_blocks(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), 4096)); }
+// What the lists would be like (SampleLists), without drawing them: a
+// workgroup's share.
+struct KeptShape {
+    unsigned int nonzero, segments, rounds, longest;
+};
+constexpr int KC_THREADS = 1024, KC_BLOCKS = 256;
 
-// koff (n + 1, from key_arena) = the exclusive scan of min(d_in, k); m[v] =
-// min(d_in(v), k); returns the number kept
-// (and, when asked, the destinations that keep any)
-static int64_t sample_offsets(const Csc& csc, int64_t n, int k, Arena& off_arena, Arena& tmp, int32_t* m,
-                              int64_t** koff, hipStream_t s, int64_t* nonzero = nullptr) {
-    if (k < 1 || k > FANOUT_MAX) fail(TAURUS_E_INVALID, "fanout %d outside [1, %d]", k, FANOUT_MAX);
-    *koff = off_arena.alloc<int64_t>(n + 1, "kept before each destination");
-    unsigned long long* dnz = nullptr;
-    if (nonzero) {
-        dnz = tmp.alloc<unsigned long long>(1, "destinations with kept in-edges");
-        fill_i32(reinterpret_cast<int32_t*>(dnz), 2, 0, s);
+// kept per destination, min(d_in(v), k), and (shape not null) each
+// workgroup's KeptShape, which the host adds up (four atomics a workgroup on
+// one line took 23 of 28 us at 300K vertices)
+__global__ __launch_bounds__(KC_THREADS) void k_sample_counts(const int64_t* __restrict__ in_off, int64_t n, int k,
+                                                              int32_t* __restrict__ m, int nchunks,
+                                                              KeptShape* __restrict__ shape) {
+    __shared__ unsigned int part[KC_THREADS / 64][4];
+    const int lane = threadIdx.x & 63;
+    unsigned int c[4] = {};
+    for (int64_t v0 = (int64_t)blockIdx.x * KC_THREADS; v0 < n; v0 += (int64_t)gridDim.x * KC_THREADS) {  // uniform
+        const int64_t v = v0 + threadIdx.x;
+        int x = 0;
+        if (v < n) m[v] = x = (int)min(in_off[v + 1] - in_off[v], (int64_t)k);
+        if (!shape) continue;
+        c[0] += x > 0;
+        c[1] += min(x, nchunks);
+#pragma unroll
+        for (int o = 8; o >= 1; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
+        if ((lane & 15) == 0) c[2] += x;
+        c[3] = max(c[3], (unsigned int)x);
     }
-    k_sample_counts<<<count_blocks(n), 256, 0, s>>>(csc.in_off, n, k, m, dnz);
+    if (!shape) return;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            const unsigned int y = __shfl_xor(c[j], o, 64);
+            c[j] = j < 3 ? c[j] + y : max(c[j], y);
+        }
+        if (lane == 0) part[threadIdx.x >> 6][j] = c[j];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int j = threadIdx.x;
+        unsigned int t = 0;
+        for (int w = 0; w < KC_THREADS / 64; w++) t = j < 3 ? t + part[w][j] : max(t, part[w][j]);
+        reinterpret_cast<unsigned int*>(shape + blockIdx.x)[j] = t;
+    }
+}
+// a workgroup's sums stay below 2^32: n < 2^31 vertices of at most FANOUT_MAX over KC_BLOCKS
+static_assert((1ll << 31) / KC_BLOCKS * FANOUT_MAX <= (1ll << 32), "32-bit sums");
+static unsigned count_blocks(int64_t n) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, KC_THREADS), KC_BLOCKS));
+}
+
+// off (n + 1, from off_arena) = the exclusive scan of min(d_in, k); m[v] =
+// min(d_in(v), k); returns the number kept (and, when asked, the rest of
+// lists' counts)
+static int64_t sample_offsets(const Csc& csc, int64_t n, int k, Arena& off_arena, Arena& tmp, int32_t* m,
+                              int64_t** off, hipStream_t s, int nchunks = 0, SampleLists* lists = nullptr) {
+    if (k < 1 || k > FANOUT_MAX) fail(TAURUS_E_INVALID, "fanout %d outside [1, %d]", k, FANOUT_MAX);
+    *off = off_arena.alloc<int64_t>(n + 1, "kept before each destination");
+    const unsigned nb = count_blocks(n);
+    KeptShape* dshape = lists ? tmp.alloc<KeptShape>(nb, "shape of the sample") : nullptr;
+    k_sample_counts<<<nb, KC_THREADS, 0, s>>>(csc.in_off, n, k, m, nchunks, dshape);
     TAURUS_CHECK_LAUNCH();
-    scan_i32_to_i64(m, *koff, n, true, tmp, s);
+    scan_i32_to_i64(m, *off, n, true, tmp, s);
     int64_t kept = 0;
+    KeptShape shape[KC_BLOCKS];
     Readback rb;
-    rb.add(&kept, *koff + n, 1);
-    if (nonzero) rb.add(reinterpret_cast<unsigned long long*>(nonzero), dnz, 1);
+    rb.add(&kept, *off + n, 1);
+    if (lists) rb.add(shape, dshape, nb);
     rb.run(s);
+    if (lists) {
+        for (unsigned b = 0; b < nb; b++) {
+            lists->nonzero += shape[b].nonzero;
+            lists->segments += shape[b].segments;
+            lists->rounds += shape[b].rounds;
+            lists->longest = std::max<int64_t>(lists->longest, shape[b].longest);
+        }
+    }
     return kept;
 }
 
@@ -649,10 +685,18 @@ static void item_buffers(int64_t kept, Arena& key_arena, Arena& val_arena, SortB
 }
 
 int64_t sample_items(const Csc& csc, int64_t n, uint64_t seed, int layer, int k, int64_t C, int vbits,
-                     Arena& key_arena, Arena& val_arena, SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad,
-                     hipStream_t s) {
+                     const SampleLists* known, Arena& key_arena, Arena& val_arena, SortBuffers& sb, int32_t* m,
+                     int32_t* first_chunk, int* bad, hipStream_t s) {
     int64_t* koff = nullptr;
-    const int64_t kept = sample_offsets(csc, n, k, key_arena, key_arena, m, &koff, s);
+    int64_t kept = 0;
+    if (known) {
+        koff = known->off;
+        kept = known->kept;
+        k_sample_counts<<<count_blocks(n), KC_THREADS, 0, s>>>(koff, n, FANOUT_MAX, m, 0, nullptr);
+        TAURUS_CHECK_LAUNCH();
+    } else {
+        kept = sample_offsets(csc, n, k, key_arena, key_arena, m, &koff, s);
+    }
     item_buffers(kept, key_arena, val_arena, sb);
     if (kept > 0)
         sample_pass(csc, n, seed, layer, k,
@@ -661,26 +705,24 @@ int64_t sample_items(const Csc& csc, int64_t n, uint64_t seed, int layer, int k,
     return kept;
 }
 
-bool sample_lists(const Csc& csc, int64_t n, int64_t e, uint64_t seed, int layer, int k, Arena& arena, Arena& tmp,
-                  SampleLists& out, int* bad, hipStream_t s) {
+void sample_shape(const Csc& csc, int64_t n, int k, int64_t nchunks, Arena& arena, Arena& tmp, SampleLists& out,
+                  hipStream_t s) {
     int32_t* m = tmp.alloc<int32_t>(n, "kept per destination");
-    out.kept = sample_offsets(csc, n, k, arena, tmp, m, &out.off, s, &out.nonzero);
-    if (out.kept == e) {
-        arena.free_ptr(out.off);
-        out = SampleLists{};
-        return false;
-    }
-    out.src = arena.alloc<uint32_t>(std::max<int64_t>(out.kept, 1), "kept sources");
-    if (out.kept > 0)
+    out.kept = sample_offsets(csc, n, k, arena, tmp, m, &out.off, s, (int)std::min<int64_t>(nchunks, FANOUT_MAX), &out);
+}
+
+void sample_lists(const Csc& csc, int64_t n, uint64_t seed, int layer, int k, Arena& arena, Arena& tmp,
+                  SampleLists& l, int* bad, hipStream_t s) {
+    l.src = arena.alloc<uint32_t>(std::max<int64_t>(l.kept, 1), "kept sources");
+    if (l.kept > 0)
         sample_pass(csc, n, seed, layer, k,
-                    SampleOut{nullptr, out.src, out.off, 1, 1, nullptr, nullptr, nullptr, bad, nullptr}, tmp, s);
-    return true;
+                    SampleOut{nullptr, l.src, l.off, 1, 1, nullptr, nullptr, nullptr, bad, nullptr}, tmp, s);
 }
 
 int64_t list_items(const SampleLists& l, int64_t n, int64_t C, int vbits, Arena& key_arena, Arena& val_arena,
                    SortBuffers& sb, int32_t* m, int32_t* first_chunk, int* bad, hipStream_t s) {
     item_buffers(l.kept, key_arena, val_arena, sb);
-    k_sample_counts<<<count_blocks(n), 256, 0, s>>>(l.off, n, FANOUT_MAX, m, nullptr);
+    k_sample_counts<<<count_blocks(n), KC_THREADS, 0, s>>>(l.off, n, FANOUT_MAX, m, 0, nullptr);
     TAURUS_CHECK_LAUNCH();
     if (l.kept > 0) {
         // every list is copied whole: a kept list is at most FANOUT_MAX long

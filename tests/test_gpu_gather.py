@@ -488,3 +488,30 @@ def test_gcn_norms_of_hub_sources(torch_cuda, n, hubs):
     words, _ = L.sampled_edges()
     L.destroy()
     _check(out, _reference(GCN, n, src, dst, words, x.double().numpy(), W, b, False, 32), F32)
+
+
+def test_long_lists_of_few_chunks_are_broadcast(torch_cuda):
+    """Lists that read more as input rows than as transformed rows added up
+    per chunk: broadcast, from the sample's offsets (no lists are drawn), with
+    the bits and statistics of a profiled layer."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n = 30_000
+    g = torch.Generator(device="cuda").manual_seed(8)
+    u, v = (torch.randint(0, n, (6_000_000,), generator=g, device="cuda") for _ in range(2))
+    key = torch.unique((u * n + v)[u != v])
+    row_off, col_dst = T.build_csr(n, (key // n).int(), (key % n).int())
+    got = []
+    for profile in (1, 0):
+        if not profile:
+            _fail_alloc("kept sources")
+        L, x, _, _, out = _layer(torch, n, row_off, col_dst, GIN, 256, 128, F32, F32, 190, chunk=65536,
+                                 profile=profile)
+        _fail_alloc(None)
+        L.push_all(x.cuda())
+        got.append((L.finalize(), out))
+        L.destroy()
+    assert torch.equal(got[0][1], got[1][1])
+    assert 0 < got[0][0]["messages"] < key.numel()
+    for k in ("messages", "pairs", "short_units", "wave_units", "split_segments", "completed"):
+        assert got[0][0][k] == got[1][0][k], k
