@@ -149,21 +149,33 @@ __global__ __launch_bounds__(256) void k_tree_sizes(const int32_t* __restrict__ 
     if (threadIdx.x == 0 && sum) atomicAdd(&size[0], sum);
 }
 
+constexpr int XP_THREADS = 256, XP_PIECE = 1024, XP_BUF = 2048, XP_FLUSH = XP_BUF - XP_THREADS;
+
 // roots, in rank order: the vertex of rank r is one when its label is r.  A
 // root takes the first slot of its tree; those with a search list form the
-// first frontier, in position order (flag, then k_root_frontier).
-__global__ void k_roots(const int32_t* __restrict__ label, const uint32_t* __restrict__ order,
+// first frontier, in position order (flag, then k_root_frontier).  *npieces =
+// the pieces that all lists of more than XP_PIECE entries make.
+__global__ __launch_bounds__(256) void k_roots(const int32_t* __restrict__ label, const uint32_t* __restrict__ order,
                         const int64_t* __restrict__ off, const int64_t* __restrict__ list_off, int64_t n,
-                        int32_t* __restrict__ pos, int32_t* __restrict__ next, int32_t* __restrict__ flag) {
+                        int32_t* __restrict__ pos, int32_t* __restrict__ next, int32_t* __restrict__ flag,
+                        unsigned long long* __restrict__ npieces) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const uint32_t v = order[r];
-    const bool root = label[v] == (int32_t)r;
-    if (root) {
-        pos[v] = (int32_t)off[r];
-        next[r] = 1;
+    int64_t np = 0;
+    if (r < n) {
+        const uint32_t v = order[r];
+        const bool root = label[v] == (int32_t)r;
+        if (root) {
+            pos[v] = (int32_t)off[r];
+            next[r] = 1;
+        }
+        const int64_t d = list_off[v + 1] - list_off[v];
+        flag[r] = root && d > 0 ? 1 : 0;
+        if (d > XP_PIECE) np = (d + XP_PIECE - 1) / XP_PIECE;
     }
-    flag[r] = root && list_off[v + 1] > list_off[v] ? 1 : 0;
+    if (!__ballot(np > 0)) return;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) np += __shfl_xor(np, o, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(npieces, (unsigned long long)np);
 }
 __global__ void k_root_frontier(const uint32_t* __restrict__ order, const int32_t* __restrict__ flag,
                                 const int64_t* __restrict__ at, int64_t n, int32_t* __restrict__ frontier) {
@@ -180,8 +192,6 @@ __global__ void k_root_frontier(const uint32_t* __restrict__ order, const int32_
 // level up: 4.7 of 7.2 ms of kernel time at 1M vertices and 20M edges, now
 // 0.62).  Candidates gather in LDS and leave XP_FLUSH or more at a time, with
 // one atomic on the shared count each.
-constexpr int XP_THREADS = 256, XP_PIECE = 1024, XP_BUF = 2048, XP_FLUSH = XP_BUF - XP_THREADS;
-
 struct Candidates {
     int32_t* buf;            // LDS, XP_BUF
     unsigned int* n;         // LDS
@@ -245,8 +255,8 @@ __global__ __launch_bounds__(XP_THREADS) void k_expand(
                 len = (int)d;
             }
         }
-        // XP_PIECE entries at most: four rounds of 256 a workgroup pass, each
-        // adding at most XP_THREADS candidates
+        // XP_PIECE entries at most: 16 rounds of 64 a wave, each adding at
+        // most XP_THREADS candidates from the workgroup
         for (int k0 = 0; k0 < XP_PIECE; k0 += 64) {
             if (__syncthreads_or(k0 < len) == 0) break;  // uniform
             const bool valid = k0 + lane < len;
@@ -257,8 +267,14 @@ __global__ __launch_bounds__(XP_THREADS) void k_expand(
     flush_candidates(c, &base, true);
 }
 
+// The noted pieces, a workgroup each; or, of a small frontier (pieces null),
+// every list, `slices` workgroups a list taking its pieces in turn: one launch
+// instead of k_expand's and this one's.  A level of a few vertices is about 25
+// us of launches, and the synchronisation that ends it took 30 us more with a
+// further launch before it (a chain of 4,000 vertices behind one hub: 101 ms,
+// 240 with both launches a level).
 __global__ __launch_bounds__(XP_THREADS) void k_expand_pieces(
-    const int32_t* __restrict__ frontier, const int2* __restrict__ pieces,
+    const int32_t* __restrict__ frontier, int64_t nf, int slices, const int2* __restrict__ pieces,
     const unsigned long long* __restrict__ piece_count, const int64_t* __restrict__ list_off,
     const int32_t* __restrict__ list_adj, const int32_t* __restrict__ label, const int32_t* __restrict__ pos,
     int32_t* __restrict__ claim, int32_t* __restrict__ cand, unsigned long long* __restrict__ count) {
@@ -268,16 +284,19 @@ __global__ __launch_bounds__(XP_THREADS) void k_expand_pieces(
     if (threadIdx.x == 0) nbuf = 0;
     __syncthreads();
     const Candidates c{buf, &nbuf, cand, count};
-    const int64_t np = (int64_t)*piece_count;
+    const int64_t np = pieces ? (int64_t)*piece_count : nf * slices;
     for (int64_t p = blockIdx.x; p < np; p += gridDim.x) {  // uniform over the workgroup
-        const int2 q = pieces[p];
+        const int2 q = pieces ? pieces[p] : make_int2((int)(p / slices), (int)(p % slices));
         const int32_t x = frontier[q.x];
         const int32_t lx = label[x];
-        const int64_t a = list_off[x] + (int64_t)q.y * XP_PIECE, e = min(a + XP_PIECE, list_off[x + 1]);
-        for (int64_t k0 = a; k0 < e; k0 += XP_THREADS) {    // uniform
-            const int64_t k = k0 + threadIdx.x;
-            expand_entry(k < e, k < e ? list_adj[k] : 0, q.x, lx, label, pos, claim, c);
-            flush_candidates(c, &base, false);
+        const int64_t end = list_off[x + 1], step = pieces ? end : (int64_t)slices * XP_PIECE;
+        for (int64_t a = list_off[x] + (int64_t)q.y * XP_PIECE; a < end; a += step) {  // uniform
+            const int64_t e = min(a + XP_PIECE, end);
+            for (int64_t k0 = a; k0 < e; k0 += XP_THREADS) {
+                const int64_t k = k0 + threadIdx.x;
+                expand_entry(k < e, k < e ? list_adj[k] : 0, q.x, lx, label, pos, claim, c);
+                flush_candidates(c, &base, false);
+            }
         }
     }
     flush_candidates(c, &base, true);
@@ -401,15 +420,18 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
     int32_t* start = tmp.alloc<int32_t>(n, "run starts");
     int32_t* frontier = tmp.alloc<int32_t>(n, "frontier");
     int32_t* cand = tmp.alloc<int32_t>(n, "candidates");
-    // [0] candidates, [1] pieces of the level's long lists; a list's pieces
-    // are at most twice its entries / XP_PIECE
-    unsigned long long* count = tmp.alloc<unsigned long long>(2, "counts");
+    // [0] candidates, [1] pieces of the level's long lists (a list's pieces
+    // are at most twice its entries / XP_PIECE), [2] pieces of all lists
+    unsigned long long* count = tmp.alloc<unsigned long long>(3, "counts");
+    unsigned long long all_pieces = 0;
+    fill_i32(reinterpret_cast<int32_t*>(count + 2), 2, 0, s);
     int2* pieces = tmp.alloc<int2>(2 * (sp.list_e / XP_PIECE) + 1, "list pieces");
     int64_t nf = 0, nroots = 0;
     {
         int32_t* rflag = cand;                      // free until the first level
         int64_t* rat = tmp.alloc<int64_t>(n + 1, "root positions");
-        k_roots<<<blocks(n), T, 0, s>>>(label, order, off, sp.list_off, n, pos, next, rflag);
+        k_roots<<<blocks(n), T, 0, s>>>(label, order, off, sp.list_off, n, pos, next, rflag,
+                                     count + 2);
         TAURUS_CHECK_LAUNCH();
         scan_i32_to_i64(rflag, rat, n, true, tmp, s);
         k_root_frontier<<<blocks(n), T, 0, s>>>(order, rflag, rat, n, frontier);
@@ -419,6 +441,7 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
         Readback rb;
         rb.add(&nf, rat + n, 1);
         rb.add(&nroots, rsum + n, 1);
+        rb.add(&all_pieces, count + 2, 1);
         rb.run(s);
         tmp.free_ptr(rsum);
         tmp.free_ptr(rat);
@@ -436,13 +459,21 @@ static void search_order(int64_t n, const Search& sp, int32_t* new_of_old, hipSt
     int64_t visited = nroots;
     while (nf > 0) {
         fill_i32(reinterpret_cast<int32_t*>(count), 4, 0, s);
-        k_expand<<<(unsigned)std::min<int64_t>(ceil_div(nf, XP_THREADS / 64), xgrid), XP_THREADS, 0, s>>>(
-            frontier, nf, sp.list_off, sp.list_adj, label, pos, claim, pieces, count + 1, cand, count);
-        TAURUS_CHECK_LAUNCH();
-        if (sp.list_e > XP_PIECE) {  // else no list is longer than a piece
-            k_expand_pieces<<<(unsigned)xgrid, XP_THREADS, 0, s>>>(frontier, pieces, count + 1, sp.list_off,
-                                                                   sp.list_adj, label, pos, claim, cand, count);
+        const int64_t slices = std::min<int64_t>((int64_t)all_pieces, xgrid / nf);
+        if (all_pieces > 0 && slices >= std::min<int64_t>((int64_t)all_pieces, 16)) {
+            k_expand_pieces<<<(unsigned)(nf * slices), XP_THREADS, 0, s>>>(frontier, nf, (int)slices, nullptr, nullptr,
+                                                                        sp.list_off, sp.list_adj, label, pos, claim,
+                                                                        cand, count);
             TAURUS_CHECK_LAUNCH();
+        } else {
+            k_expand<<<(unsigned)std::min<int64_t>(ceil_div(nf, XP_THREADS / 64), xgrid), XP_THREADS, 0, s>>>(
+                frontier, nf, sp.list_off, sp.list_adj, label, pos, claim, pieces, count + 1, cand, count);
+            TAURUS_CHECK_LAUNCH();
+            if (all_pieces > 0) {
+                k_expand_pieces<<<(unsigned)std::min<int64_t>((int64_t)all_pieces, xgrid), XP_THREADS, 0, s>>>(
+                    frontier, nf, 0, pieces, count + 1, sp.list_off, sp.list_adj, label, pos, claim, cand, count);
+                TAURUS_CHECK_LAUNCH();
+            }
         }
         unsigned long long nc = 0;
         {

@@ -311,3 +311,24 @@ def test_reorder_list_pieces(torch_cuda, d):
     row_off, col_dst = T.build_csr(n, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda())
     assert np.array_equal(T.reorder(n, row_off, col_dst).cpu().numpy(), O.reorder_bfs(g))
     assert np.array_equal(T.reorder_rcm(n, row_off, col_dst).cpu().numpy(), O.reorder_rcm(g))
+
+
+@pytest.mark.parametrize("hub", [1024, 1025, 5000])
+def test_reorder_many_levels_and_a_hub(torch_cuda, hub):
+    """A long chain (a level per vertex) that ends in a hub, and a second one
+    whose levels are 600 wide: small frontiers take a list's pieces in one
+    launch, wide ones note them; degree/BFS and RCMK orders equal the oracle's."""
+    import oracle as O
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    _note(f"reorder many levels hub={hub}")
+    n = 12_000
+    i = np.arange(300)
+    w = np.arange(3000)                                     # five levels of 600
+    u = np.concatenate([i + 1, 1000 + np.arange(hub), 6000 + w + 600, np.full(600, 0), 6000 + np.arange(600)])
+    v = np.concatenate([i, np.full(hub, 300), 6000 + w, 6000 + np.arange(600), np.full(600, 11_999)])
+    src, dst = _simple(n, u, v)[:2]
+    g = O.Graph(n, src, dst)
+    row_off, col_dst = T.build_csr(n, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda())
+    assert np.array_equal(T.reorder(n, row_off, col_dst).cpu().numpy(), O.reorder_bfs(g))
+    assert np.array_equal(T.reorder_rcm(n, row_off, col_dst).cpu().numpy(), O.reorder_rcm(g))
