@@ -304,12 +304,22 @@ __global__ __launch_bounds__(256) void k_res_victims_dev(int64_t n, int32_t k, c
     }
 }
 
+// The free-list top once chunk number seq has its rows, for the host to see
+// when it gets round to it (Residency::prepare).
+__device__ inline void res_report(unsigned long long* mail, uint32_t seq, int32_t top) {
+    __hip_atomic_store(mail, ((unsigned long long)seq << 32) | (uint32_t)top, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // after the assignment: the free-list top, the evictions made, and the
 // counters of the next chunk
 __global__ void k_res_settle(int32_t* __restrict__ top, unsigned long long* __restrict__ listed,
                              unsigned long long* __restrict__ chosen, ResPlan* __restrict__ plan,
-                             unsigned long long* __restrict__ evictions) {
-    *top += (int32_t)plan->victims - (int32_t)*listed;
+                             unsigned long long* __restrict__ evictions, unsigned long long* __restrict__ mail,
+                             uint32_t seq) {
+    const int32_t left = *top + (int32_t)plan->victims - (int32_t)*listed;
+    *top = left;
+    res_report(mail, seq, left);
     if ((int64_t)*chosen != plan->victims) plan->bad = 1;
     *evictions += (unsigned long long)plan->victims;
     *listed = 0;
@@ -392,8 +402,11 @@ __global__ __launch_bounds__(256) void k_res_assign(const int32_t* __restrict__ 
 }
 
 // free-list top after a device-counted assignment: *top -= listed
-__global__ void k_res_take(int32_t* __restrict__ top, const unsigned long long* __restrict__ listed) {
-    *top -= (int32_t)*listed;
+__global__ void k_res_take(int32_t* __restrict__ top, const unsigned long long* __restrict__ listed,
+                           unsigned long long* __restrict__ mail, uint32_t seq) {
+    const int32_t left = *top - (int32_t)*listed;
+    *top = left;
+    res_report(mail, seq, left);
 }
 
 // touched vertices that completed give their slot back (hub slots stay)
@@ -545,8 +558,13 @@ Residency::Residency(hipStream_t s, int64_t n_, int d_o_, int64_t slots, int64_t
     on_device = one_key && ceil_div(n, RES_WTILE) <= 16384;
     hub_share = messages > 0 ? (double)hub_msgs / (double)messages : 0.0;
     // host store for evicted rows: pinned, written and read by kernels only
-    store_host = static_cast<float*>(pinned_acquire((size_t)n * d_o * sizeof(float), &store_cap));
+    // and, behind the rows, what the device reports (res_report)
+    const size_t rows = (size_t)n * d_o * sizeof(float);
+    store_host = static_cast<float*>(pinned_acquire(rows + sizeof(unsigned long long), &store_cap));
     TAURUS_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&store_dev), store_host, 0));
+    mail_host = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(store_host) + rows);
+    mail_dev = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(store_dev) + rows);
+    __atomic_store_n(mail_host, 0ull, __ATOMIC_RELAXED);
 }
 
 Residency::~Residency() {
@@ -557,6 +575,15 @@ Residency::~Residency() {
 void Residency::prepare(const ResChunk& c, int32_t k, const int2* cnt, hipStream_t s) {
     const int T = 256;
     const int64_t total = c.total();
+    // what the device last reported, less what the chunks queued since may
+    // have taken, is a lower bound too (evictions and releases only raise it)
+    const uint64_t mail = __atomic_load_n(mail_host, __ATOMIC_RELAXED);
+    if ((mail >> 32) > reported) {
+        reported = mail >> 32;
+        free_lb = std::max(free_lb, (int64_t)(uint32_t)mail - (taken_most.back() - taken_most[(size_t)reported]));
+    }
+    const uint32_t seq = (uint32_t)taken_most.size();
+    taken_most.push_back(taken_most.back() + total);
     unsigned long long* need_count = counters;
     if (!counters_clear) fill_i32(reinterpret_cast<int32_t*>(need_count), 2, 0, s);
     counters_clear = false;
@@ -572,7 +599,7 @@ void Residency::prepare(const ResChunk& c, int32_t k, const int2* cnt, hipStream
                 need, 0, need_count, d_o, free_list, 0, free_top, nullptr, k, pool, store_dev, slot_of, evicted, want,
                 adm, reloads_of, counters + 2);
             TAURUS_CHECK_LAUNCH();
-            k_res_take<<<1, 1, 0, s>>>(free_top, need_count);
+            k_res_take<<<1, 1, 0, s>>>(free_top, need_count, mail_dev, seq);
             TAURUS_CHECK_LAUNCH();
         }
         free_lb -= total;
@@ -602,10 +629,10 @@ void Residency::prepare(const ResChunk& c, int32_t k, const int2* cnt, hipStream
         k_res_assign<<<rows, T, 0, s>>>(need, 0, need_count, d_o, free_list, 0, free_top, plan, k, pool, store_dev,
                                         slot_of, evicted, want, adm, reloads_of, counters + 2);
         TAURUS_CHECK_LAUNCH();
-        k_res_settle<<<1, 1, 0, s>>>(free_top, need_count, chosen, plan, counters + 4);
+        k_res_settle<<<1, 1, 0, s>>>(free_top, need_count, chosen, plan, counters + 4, mail_dev, seq);
         TAURUS_CHECK_LAUNCH();
         counters_clear = true;
-        free_lb = 0;
+        free_lb = std::max<int64_t>(0, free_lb - total);
         return;
     }
     unsigned long long nn = 0;

@@ -71,6 +71,9 @@ private:
     // are assigned without reading anything back (releases only raise the
     // true count)
     int64_t free_lb = 0;
+    std::vector<int64_t> taken_most{0};  // rows the chunks so far may have taken, before and after each
+    uint64_t reported = 0;               // chunks whose report has been read
+    unsigned long long *mail_host = nullptr, *mail_dev = nullptr;  // chunk << 32 | free-list top (res_report)
     bool on_device = false;        // evictions are decided by kernels (k_res_threshold)
     bool counters_clear = false;   // the listed count is already zero
     int64_t host_evictions = 0;    // decided on the host

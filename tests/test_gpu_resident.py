@@ -136,6 +136,45 @@ def test_eviction_policies_match_oracle_simulation(torch_cuda, policy):
     assert np.array_equal(hist, np.bincount(np.minimum(per, 63), minlength=64))
 
 
+@pytest.mark.parametrize("share", [0.3, 0.4, 0.9])
+def test_free_rows_reported_by_the_device(torch_cuda, share):
+    """Pushes that wait for each chunk, so that the host has seen the device's
+    count of free rows and takes the short path between evictions: the same
+    output, evictions, reloads and histogram as the simulation, and as pushes
+    queued at once."""
+    import oracle as O
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    w = dataclasses.replace(WL.SAGE_OOC_RMAT_269M, random_ids=True).scaled(n=1 << 16, e=1 << 20, chunk=512)
+    src, dst = WL.graph(w)
+    _note(f"free rows reported: pool {share}")
+    row_off, col_dst = H.gpu_graph(w, src, dst)
+    X = torch.from_numpy(WL.input_features(w)).cuda()
+    spec = H.layer_specs(w)[0]
+    ref = torch.empty((w.n, spec["d_out"]), dtype=torch.float32, device="cuda")
+    L = T.Layer(w.n, row_off, col_dst, out=ref, chunk=w.chunk, **spec)
+    L.push_all(X)
+    st0 = L.finalize()
+    L.destroy()
+    budget = H.pool_budget(st0, w.n, spec["d_out"], spec["d_in"], w.chunk, int(share * w.n))
+    g = O.Graph(w.n, src, dst)
+    for wait in (True, False):
+        out = torch.empty_like(ref)
+        L = T.Layer(w.n, row_off, col_dst, out=out, chunk=w.chunk, hbm_budget=budget, hub_fraction=0.01, **spec)
+        for b in range(0, w.n, w.chunk):
+            L.push_chunk(b, min(w.n, b + w.chunk), X[b:b + w.chunk])
+            if wait:
+                torch.cuda.synchronize()
+        st = L.finalize()
+        hist = L.reload_histogram(64)
+        L.destroy()
+        assert torch.equal(out, ref)
+        _note(f"  pool {st['pool_rows']} rows: {st['evictions']} evictions, {st['reloads']} reloads")
+        ev, rl, per = O.residency_sim(g, w.chunk, st["pool_rows"], st["hub_rows"], "pending")
+        assert (st["evictions"], st["reloads"]) == (ev, rl)
+        assert np.array_equal(hist, np.bincount(np.minimum(per, 63), minlength=64))
+
+
 def big_pending_graph(groups=4, per=4, chunks_per_group=48, chunk=512, seed=3):
     """16 destinations with 13,500-24,600 in-edges each: chunk k's sources
     send to the 4 destinations of group k mod 4, destination j keeping each
