@@ -2046,6 +2046,11 @@ static void join_setup(taurus_layer* L, hipStream_t s) {
     if (L->res) L->res->arena.set_stream(L->s);
 }
 
+// the scatter addresses Y with 32-bit byte offsets
+static bool chunk_addressable(const taurus_layer* L, int stride) {
+    return std::min<int64_t>(L->C, L->n) * (int64_t)stride * 4 <= (int64_t)0x7f000000;
+}
+
 static void set_widths(taurus_layer* L) {
     const taurus_layer_desc& d = L->d;
     // accumulator width: the perceptron's hidden width for GIN_MLP
@@ -2055,13 +2060,14 @@ static void set_widths(taurus_layer* L) {
     // Y rows padded to whole 128-byte lines (the padding columns hold the
     // zero-padded weights' products): the transform then writes whole lines
     // and a gathered row starts on a line
-    // (GAT keeps every vertex's row: half lines, to bound the table of a narrow output)
-    L->ystride = d.agg == TAURUS_GAT_ATT ? (L->ncols + 15) / 16 * 16 : (L->ncols + 31) / 32 * 32;
+    // (GAT keeps every vertex's row: half lines, to bound the table of a narrow
+    // output, and none where only they take the chunk past what is addressable)
+    if (d.agg != TAURUS_GAT_ATT) L->ystride = (L->ncols + 31) / 32 * 32;
+    else if (!chunk_addressable(L, L->ystride = (L->ncols + 15) / 16 * 16)) L->ystride = L->ncols;
 }
 
-// the scatter addresses Y with 32-bit byte offsets
 static void check_chunk_bytes(const taurus_layer* L) {
-    if (std::min<int64_t>(L->C, L->n) * (int64_t)L->ystride * 4 > (int64_t)0x7f000000)
+    if (!chunk_addressable(L, L->ystride))
         fail(TAURUS_E_INVALID, "chunk %lld x %d transform columns exceeds 2 GiB of fp32", (long long)L->C, L->ystride);
 }
 

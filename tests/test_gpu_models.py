@@ -285,3 +285,36 @@ def test_gin_mlp_argument_errors(torch_cuda):
         assert ex.value.status == -1, (dh, bad)
     with pytest.raises(ValueError):
         T.Layer(n, row_off, col_dst, **dict(base(8), weight2=np.zeros((4, 4), np.float32)))
+
+
+def test_gat_narrow_output_of_a_large_chunk(torch_cuda):
+    """34M vertices in one chunk at 4 output columns: rows padded to 16 floats
+    would pass the 2 GiB a chunk can address, rows of 4 do not."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, d_in, d = 34_000_000, 4, 4
+    rng = np.random.default_rng(2)
+    src, dst = rng.permutation(n)[:64].astype(np.int32), rng.permutation(1000)[:64].astype(np.int32)
+    row_off, col_dst = T.build_csr(n, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda())
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((n, d_in), generator=g, device="cuda")
+    W = rng.standard_normal((d_in, d)).astype(np.float32)
+    attn = rng.uniform(-0.3, 0.3, (2, d)).astype(np.float32)
+    b = rng.uniform(-0.1, 0.1, d).astype(np.float32)
+    out = torch.empty((n, d), device="cuda")
+    L = T.Layer(n, row_off, col_dst, agg=3, d_in=d_in, d_out=d, weight_cat=W, bias=b, out=out, attn=attn,
+                chunk=1 << 26)
+    L.push_all(x)
+    st = L.finalize()
+    L.destroy()
+    assert st["completed"] == n
+    Wd, bd, ad = (torch.from_numpy(t).cuda().double() for t in (W, b, attn))
+    z = x @ Wd.float()
+    assert float((z + bd.float() - out).abs()[1000:].max()) < 1e-4      # no in-edges: the vertex itself
+    h = x.double()[torch.from_numpy(np.concatenate([src, dst])).cuda().long()] @ Wd
+    hu, hv = h[:64], h[64:]
+    e = torch.nn.functional.leaky_relu(torch.stack([hu @ ad[0], hv @ ad[0]]) + hv @ ad[1], 0.2)
+    w = torch.softmax(e, 0)
+    ref = w[0][:, None] * hu + w[1][:, None] * hv + bd
+    got = out[torch.from_numpy(dst).cuda().long()].double()
+    assert float((ref - got).abs().max()) < 1e-5
