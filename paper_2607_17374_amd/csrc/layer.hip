@@ -1384,8 +1384,10 @@ struct ChunkIndex {
     double ms_build = 0;
     // GIN perceptron layers: the vertices grouped by the chunk they complete
     // in (build_completion_lists), chunk k's at [comp_off[k], comp_off[k + 1]);
-    // built by the first layer that needs them
+    // built by the first layer that needs them, in memory of their own: a
+    // budgeted layer over the same plan counts the rest of the index alone
     std::mutex comp_mu;
+    Arena comp_arena;
     int32_t* comp_ids = nullptr;
     std::vector<int64_t> comp_off;
     ChunkIndex(hipStream_t s, int64_t budget) : arena(s, budget), built_on(s) {}
@@ -1396,6 +1398,8 @@ struct ChunkIndex {
         if (ready) (void)hipEventDestroy(ready);
         arena.set_stream(nullptr);
         arena.release();
+        comp_arena.set_stream(nullptr);
+        comp_arena.release();
     }
     const int4* list_at(int l, int64_t k) const { return units + list_off[l][(size_t)k]; }
     int64_t list_count(int l, int64_t k) const {
@@ -1967,8 +1971,8 @@ static void build_completion_lists(ChunkIndex& idx, Arena& tmp, hipStream_t s) {
     int64_t* off = tmp.alloc<int64_t>(nch + 1, "graduation list positions");
     k_chunk_starts<<<(unsigned)ceil_div(n, T), T, 0, s>>>(sb.keys[sb.cur], n, nch, off);
     TAURUS_CHECK_LAUNCH();
-    idx.arena.set_stream(s);
-    int32_t* ids = idx.arena.alloc<int32_t>(n, "graduation lists");
+    idx.comp_arena.set_stream(s);
+    int32_t* ids = idx.comp_arena.alloc<int32_t>(n, "graduation lists");
     TAURUS_HIP(hipMemcpyAsync(ids, sb.vals[sb.cur], (size_t)n * 4, hipMemcpyDeviceToDevice, s));
     idx.comp_off.assign((size_t)nch + 1, 0);
     int hbad = 0;
@@ -2934,6 +2938,7 @@ static int finalize(taurus_layer* L, taurus_stats* st) {
         st->wave_units = idx.n_list[NCLASS];
         st->split_segments = idx.n_list[NCLASS + 1];
         st->device_bytes = L->arena.peak() + (L->ms_index > 0 ? idx.arena.peak() : 0);
+        if (L->d.agg == TAURUS_GIN_MLP) st->device_bytes += idx.comp_arena.peak();
         st->ms_init = L->ms_init;
         st->ms_index = L->ms_index;
         const int64_t row_bytes = (int64_t)L->d_o * 4;

@@ -175,6 +175,35 @@ def test_free_rows_reported_by_the_device(torch_cuda, share):
         assert np.array_equal(hist, np.bincount(np.minimum(per, 63), minlength=64))
 
 
+def test_completion_lists_do_not_count_in_a_budget(torch_cuda):
+    """A GIN perceptron layer leaves its completion lists in the plan's chunk
+    index: a budgeted layer over the same plan has the pool it had before."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    w = WL.SAGE_OOC_RMAT_269M.scaled(n=1 << 16, e=1 << 19, chunk=512)
+    row_off, col_dst = H.gpu_graph(w)
+    X = torch.from_numpy(WL.input_features(w)).cuda()
+    spec = H.layer_specs(w)[0]
+    out = torch.empty((w.n, spec["d_out"]), device="cuda")
+    plan = T.Plan(w.n, row_off, col_dst, w.chunk)
+
+    def run(**kw):
+        L = T.Layer(w.n, row_off, col_dst, out=out, chunk=w.chunk, plan=plan, **{**spec, **kw})
+        L.push_all(X)
+        st = L.finalize()
+        L.destroy()
+        return st
+
+    budget = H.pool_budget(run(), w.n, spec["d_out"], spec["d_in"], w.chunk, int(0.4 * w.n))
+    pool = run(hbm_budget=budget, hub_fraction=0.01)["pool_rows"]
+    rng = np.random.default_rng(1)
+    d = spec["d_out"]
+    run(agg=4, d_hidden=d, weight_cat=rng.uniform(-0.1, 0.1, (spec["d_in"], d)).astype(np.float32),
+        weight2=rng.uniform(-0.1, 0.1, (d, d)).astype(np.float32))
+    assert run(hbm_budget=budget, hub_fraction=0.01)["pool_rows"] == pool > 0
+    plan.destroy()
+
+
 def big_pending_graph(groups=4, per=4, chunks_per_group=48, chunk=512, seed=3):
     """16 destinations with 13,500-24,600 in-edges each: chunk k's sources
     send to the 4 destinations of group k mod 4, destination j keeping each
