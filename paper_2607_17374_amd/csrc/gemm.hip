@@ -113,7 +113,10 @@ static void launch_panel(const void* X, int64_t M, int K, const void* Wp, int Nc
     const bool narrow = NBP <= 4 || panels * ceil_div(NBP, 8) < cus;
     if (narrow) {
         dim3 grid((unsigned)panels, (unsigned)ceil_div(NBP, 4));
-        k_gemm_panel<DT, 4, 2 * PIPE_KS><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);
+        if (ceil_div(K, GemmOp<DT>::KBLK) > PIPE_KS)
+            k_gemm_panel<DT, 4, 2 * PIPE_KS><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);
+        else  // one short stage holds it all: half the LDS
+            k_gemm_panel<DT, 4, PIPE_KS><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);
     } else {
         dim3 grid((unsigned)panels, (unsigned)ceil_div(NBP, 8));
         k_gemm_panel<DT, 8, PIPE_KS><<<grid, 256, 0, s>>>(X, M, K, w, NBP, Nc, rscale, Y, stream, f);

@@ -318,3 +318,35 @@ def test_gat_narrow_output_of_a_large_chunk(torch_cuda):
     ref = w[0][:, None] * hu + w[1][:, None] * hv + bd
     got = out[torch.from_numpy(dst).cuda().long()].double()
     assert float((ref - got).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("d_in", [8, 32, 40, 64, 72])
+@pytest.mark.parametrize("d_out", [16, 64, 200])
+def test_transform_stage_lengths(torch_cuda, dt, d_in, d_out):
+    """Exact GIN layers around the k-blocks one short and one long stage of
+    the narrow transform hold, in chunks that leave compute units idle, against
+    float64 (a sum of at most 73 rows and 72 products: 2e-5 of the RMS)."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n = 700
+    rng = np.random.default_rng(d_in)
+    key = np.unique(rng.integers(0, n * n, 6000))
+    u, v = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    u, v = u[u != v], v[u != v]
+    row_off, col_dst = T.build_csr(n, torch.from_numpy(u).cuda(), torch.from_numpy(v).cuda())
+    td = [torch.float32, torch.bfloat16][dt]
+    x = torch.from_numpy(rng.standard_normal((n, d_in)).astype(np.float32)).to(td)
+    W = (rng.standard_normal((d_in, d_out)) / np.sqrt(d_in)).astype(np.float32)
+    out = torch.empty((n, d_out), device="cuda")
+    L = T.Layer(n, row_off, col_dst, agg=2, d_in=d_in, d_out=d_out, weight_cat=W, bias=None, out=out, in_dtype=dt,
+                chunk=192)
+    L.push_all(x.cuda())
+    L.finalize()
+    L.destroy()
+    s = x.double().numpy()
+    z = s.copy()
+    np.add.at(z, v, s[u])
+    z = z @ torch.from_numpy(W).to(td).double().numpy()
+    y = out.double().cpu().numpy()
+    assert np.all(np.abs(y - z) <= 2e-5 * (np.abs(z) + np.sqrt(np.mean(z * z))))
