@@ -515,3 +515,100 @@ def test_long_lists_of_few_chunks_are_broadcast(torch_cuda):
     assert 0 < got[0][0]["messages"] < key.numel()
     for k in ("messages", "pairs", "short_units", "wave_units", "split_segments", "completed"):
         assert got[0][0][k] == got[1][0][k], k
+
+
+def _large_graph(torch, n, e, seed):
+    import paper_2607_17374_amd as T
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    u = torch.randint(0, n, (e,), generator=g, device="cuda")
+    v = (torch.rand(e, generator=g, device="cuda") ** 3 * (n - 1)).long()   # many lists empty, some long
+    key = torch.unique((u * n + v)[u != v])
+    return key, *T.build_csr(n, (key // n).int(), (key % n).int())
+
+
+def _large_reference(torch, agg, n, key, words, xd, W, b, d_out):
+    """float64 on the GPU, before the activation; also the kept edges."""
+    keep = torch.from_numpy(np.unpackbits(words.view(np.uint8), bitorder="little")[:key.numel()].astype(bool)).cuda()
+    u, v = key[keep] // n, key[keep] % n
+    xd, W = xd.double(), torch.from_numpy(np.ascontiguousarray(W)).cuda().double()
+    d = torch.bincount(v, minlength=n).double()
+    s = torch.zeros_like(xd)
+    if agg == SAGE:
+        s.index_add_(0, v, xd[u])
+        z = (s / d.clamp(min=1)[:, None]) @ W[:, :d_out] + xd @ W[:, d_out:]
+    elif agg == GCN:
+        no = (torch.bincount(u, minlength=n) + 1).double().rsqrt()
+        s.index_add_(0, v, xd[u] * no[u][:, None])
+        z = ((s + xd * no[:, None]) * (d + 1).rsqrt()[:, None]) @ W
+    else:
+        z = (s.index_add_(0, v, xd[u]) + xd) @ W
+    return z + torch.from_numpy(b).cuda().double(), u, v
+
+
+@pytest.mark.parametrize("agg,d_in,d_out,dt,od,k", [
+    (SAGE, 104, 44, BF16, F32, 10),      # both halves' weights resident
+    (SAGE, 256, 172, BF16, F32, 5),      # halves apart, partial products added
+    (SAGE, 128, 256, F32, BF16, 6),      # fp32 weights: halves apart
+    (GCN, 64, 100, F32, F32, 7), (GIN, 128, 260, BF16, BF16, 3)])
+def test_early_finalize_of_large_layers(torch_cuda, agg, d_in, d_out, dt, od, k):
+    """The persistent kernels with chunks missing: complete rows written, the
+    others untouched, also where partial products of a skipped row were never
+    written; then the rest, in another order."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, chunk = 300_001, 65536
+    print(f"gather early finalize agg={agg} {d_in}->{d_out} dt={dt}/{od} k={k}", flush=True)
+    key, row_off, col_dst = _large_graph(torch, n, 900_000, 9)
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, d_in, d_out, dt, od, k, chunk=chunk)
+    _fail_alloc("work lists")
+    xd = x.cuda()
+    first = (4, 0, 2)
+    for c in first:
+        L.push_chunk(c * chunk, min(n, c * chunk + chunk), xd[c * chunk:c * chunk + chunk])
+    with pytest.raises(T.TaurusError) as ex:
+        L.finalize()
+    _fail_alloc(None)
+    assert ex.value.status == -5
+    words, _ = L.sampled_edges()
+    z, u, v = _large_reference(torch, agg, n, key, words, xd, W, b, d_out)
+    z = torch.relu(z)
+    here = torch.isin(torch.arange(n, device="cuda") // chunk, torch.tensor(first, device="cuda"))
+    done = here.clone()
+    done[v[~here[u]]] = False
+    assert 0 < int(done.sum()) < n
+    assert bool((out[~done] == -7.0).all())
+    _check(out[done], z[done].cpu().numpy(), od)
+    for c in (3, 1):
+        L.push_chunk(c * chunk, c * chunk + chunk, xd[c * chunk:c * chunk + chunk])
+    st = L.finalize()
+    L.destroy()
+    assert st["completed"] == n and st["pending_left"] == 0
+    _check(out, z.cpu().numpy(), od)
+
+
+@pytest.mark.parametrize("agg,d_in,d_out,dt,od,k", [
+    (SAGE, 256, 200, F32, F32, 25), (GIN, 256, 136, F32, BF16, 30), (GCN, 132, 68, F32, F32, 40),
+    (SAGE, 64, 20, BF16, F32, 100)])
+@pytest.mark.parametrize("n", [1025, 270_001])
+def test_long_lists_that_are_gathered(torch_cuda, n, agg, d_in, d_out, dt, od, k):
+    """The widest rows and the longest lists that the gather takes (refusing
+    the broadcast's work lists shows that it does), and their statistics."""
+    torch = torch_cuda
+    print(f"gather long lists n={n} agg={agg} {d_in}->{d_out} dt={dt}/{od} k={k}", flush=True)
+    key, row_off, col_dst = _large_graph(torch, n, 60 * n if n < 5000 else 8 * n, 3)
+    got = []
+    for profile in (1, 0):
+        if not profile:
+            _fail_alloc("work lists")
+        L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, d_in, d_out, dt, od, k, chunk=4096 if n > 5000 else 192,
+                                 profile=profile)
+        L.push_all(x.cuda())
+        got.append(L.finalize())
+        _fail_alloc(None)
+        words, _ = L.sampled_edges()
+        L.destroy()
+    z, u, v = _large_reference(torch, agg, n, key, words, x.cuda(), W, b, d_out)
+    assert int(torch.bincount(v).max()) == k
+    _check(out, torch.relu(z).cpu().numpy(), od)
+    for name in ("messages", "pairs", "short_units", "wave_units", "split_segments", "completed", "self_in_transform"):
+        assert got[0][name] == got[1][name], name
