@@ -3323,6 +3323,10 @@ int taurus_finalize(taurus_layer* L, taurus_stats* stats) {
     } catch (const Failure& f) {
         if (f.status == TAURUS_E_OOM || f.status == TAURUS_E_DEVICE) L->poisoned = true;
         return f.status;
+    } catch (const std::exception& x) {
+        L->poisoned = true;
+        set_error("internal error: %s", x.what());
+        return TAURUS_E_DEVICE;
     }
 }
 
@@ -3331,7 +3335,7 @@ int taurus_sampled_edges(taurus_layer* L, uint64_t* mask_bits_host, int64_t* n_k
         set_error("null argument");
         return TAURUS_E_INVALID;
     }
-    try {
+    return guarded([&] {
         const int64_t words = ceil_div(L->g.e, 64);
         if (L->csc && !L->mask && words > 0) {
             L->mask = L->arena.alloc<uint64_t>(words, "fanout mask");
@@ -3345,10 +3349,8 @@ int taurus_sampled_edges(taurus_layer* L, uint64_t* mask_bits_host, int64_t* n_k
             if (L->g.e % 64) mask_bits_host[words - 1] = (1ull << (L->g.e % 64)) - 1;
         }
         if (n_kept) *n_kept = L->gather ? L->lists.kept : L->idx->kept;
-        return TAURUS_OK;
-    } catch (const Failure& f) {
-        return f.status;
-    }
+        return (int)TAURUS_OK;
+    });
 }
 
 int64_t taurus_release_cached_memory(int64_t bytes) {
@@ -3357,6 +3359,9 @@ int64_t taurus_release_cached_memory(int64_t bytes) {
         return (int64_t)release_cached(bytes <= 0 ? 0 : (size_t)bytes);
     } catch (const Failure& f) {
         return f.status;
+    } catch (const std::exception& x) {
+        set_error("internal error: %s", x.what());
+        return TAURUS_E_DEVICE;
     }
 }
 
@@ -3365,17 +3370,15 @@ int taurus_layer_reload_histogram(taurus_layer* L, int64_t* counts, int32_t bins
         set_error("null argument or bins < 2");
         return TAURUS_E_INVALID;
     }
-    try {
+    return guarded([&] {
         if (L->res) {
             L->res->reload_histogram(counts, bins, L->s);
         } else {
             for (int b = 0; b < bins; b++) counts[b] = 0;
             counts[0] = L->n;
         }
-        return TAURUS_OK;
-    } catch (const Failure& f) {
-        return f.status;
-    }
+        return (int)TAURUS_OK;
+    });
 }
 
 void taurus_layer_destroy(taurus_layer* L) {

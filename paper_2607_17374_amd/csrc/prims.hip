@@ -359,14 +359,17 @@ void Readback::run(hipStream_t s) {
 
 // ---------------------------------------------------------------- arena -----
 // For tests of failure handling: the calling thread's next allocation of
-// device memory named `what` (alloc_bytes) fails as if there were none left.
+// device memory named `what` (alloc_bytes) fails as if there were none left,
+// or, named `!what`, throws what the C++ library would.
 static thread_local std::string t_fail_alloc;
 extern "C" void taurus_test_fail_alloc(const char* what) { t_fail_alloc = what ? what : ""; }
 
 void* Arena::alloc_bytes(int64_t bytes, const char* what) {
     if (bytes <= 0) bytes = 16;
-    if (!t_fail_alloc.empty() && t_fail_alloc == what) {
+    if (!t_fail_alloc.empty() && std::strcmp(t_fail_alloc.c_str() + (t_fail_alloc[0] == '!'), what) == 0) {
+        const bool library = t_fail_alloc[0] == '!';
         t_fail_alloc.clear();
+        if (library) throw std::bad_alloc();
         fail(TAURUS_E_OOM, "allocation of %lld bytes for %s failed on request", (long long)bytes, what);
     }
     if (region_) {

@@ -612,3 +612,29 @@ def test_long_lists_that_are_gathered(torch_cuda, n, agg, d_in, d_out, dt, od, k
     _check(out, torch.relu(z).cpu().numpy(), od)
     for name in ("messages", "pairs", "short_units", "wave_units", "split_segments", "completed", "self_in_transform"):
         assert got[0][name] == got[1][name], name
+
+
+def test_no_exception_leaves_an_entry(torch_cuda):
+    """An exception of the C++ library inside finalize or sampled_edges
+    becomes a status; a handle whose finalize threw is refused from then on."""
+    import paper_2607_17374_amd as T
+    torch = torch_cuda
+    n, chunk = 1025, 192
+    _, _, row_off, col_dst = _graph(torch, n, 6000, 3)
+    L, x, _, _, _ = _layer(torch, n, row_off, col_dst, SAGE, 64, 48, F32, F32, 6, chunk=chunk)
+    for call, what in ((L.sampled_edges, "!fanout mask"), (lambda: L.push_all(x.cuda()), "!input rows")):
+        _fail_alloc(what)
+        with pytest.raises(T.TaurusError) as ex:
+            call()
+        assert ex.value.status == -3, what
+    L.destroy()
+    L, x, _, _, _ = _layer(torch, n, row_off, col_dst, SAGE, 64, 48, F32, F32, 6, chunk=chunk)
+    L.push_all(x.cuda())
+    status = []
+    for what in ("!list counts", None):
+        _fail_alloc(what)
+        with pytest.raises(T.TaurusError) as ex:
+            L.finalize()
+        status.append(ex.value.status)
+    L.destroy()
+    assert status == [-3, -4]
