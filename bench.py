@@ -18,11 +18,13 @@ The CSR build and the layers are timed in two loops of K repetitions each
 layers' buffers do not fit in HBM), and a step's time is their sum.
 
 Output: one JSON line.  value = aggregated edges per second per layer (the
-propagated edges of all layers / step time) in GTEPS.  roofline = the
-scatter kernel's algorithmic HBM bytes over its HIP-event-timed launches,
-against 8 TB/s.  gemm_roofline = the transform's flops over its
-HIP-event-timed launches (a separate untimed pass), against
-min(bf16 MFMA peak, arithmetic intensity x HBM bandwidth).  cpu_baseline =
+propagated edges of all layers / step time) in GTEPS.  roofline = the timed
+layers' algorithmic HBM bytes (gathered_layer_bytes) over their wall time,
+set-up and sampling included, against 8 TB/s.  broadcast_roofline = the
+scatter kernel's algorithmic HBM bytes over its HIP-event-timed launches and
+gemm_roofline = the transform's flops over its own, against min(bf16 MFMA
+peak, arithmetic intensity x HBM bandwidth): both of untimed profiled passes,
+in which these layers are broadcast chunk by chunk.  cpu_baseline =
 the CPU oracle on a bounded sample: its in-lists and sampler over the whole
 graph, and the layer maths for 65,536 seeded destinations plus the 256
 largest in-degrees and up to 256 without in-edges per layer, each layer fed
@@ -553,16 +555,19 @@ def bench_rmat_1m(args):
         plan.destroy()
         return t_csr * 1e3, t_plan * 1e3, per
 
+    # per-kernel events in the first timed step only: each event pair costs
+    # about 6 us of the step.  Sampled layers run other kernels when profiled
+    # (they are broadcast): their events come from a step that is not timed
+    inside = 0 if sampled else profile
     for _ in range(args.warmup):
-        step(profile)
+        step(inside)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    # per-kernel events in the first timed step only: each event pair costs
-    # about 6 us of the step
-    runs = [step(profile if i == 0 else 0) for i in range(args.steps)]
+    runs = [step(inside if i == 0 else 0) for i in range(args.steps)]
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
     ms_step = elapsed * 1e3 / args.steps
+    events = step(profile)[2] if profile and not inside else runs[0][2]
 
     # per-layer figures, averaged over the timed steps
     nl = len(specs)
@@ -585,7 +590,7 @@ def bench_rmat_1m(args):
         if not all(checks):
             model_ok = False
             print(f"warning: layer {li + 1} work counts differ from the flush model: {checks}", file=sys.stderr)
-        prof = sts[:1] if profile else []  # the step with events
+        prof = [events[li]] if profile else []  # the step with events
         timed = ("gemm", "scatter", "fixup")
         ms = {k: float(np.mean([s[f"ms_{k}"] for s in (prof if k in timed else sts)])) if (prof or k not in timed)
               else 0.0 for k in ("gemm", "scatter", "fixup", "init", "index")}
@@ -687,6 +692,17 @@ def sampled_scatter_bytes(st: dict, n: int, d_o: int, out_bytes: int, sage: bool
     y_rows = n * (2 if sage else 1) - A
     return (16.0 * units + 4.0 * st["messages"] + 4.0 * d_o * y_rows + 1.0 * n + 12.0 * P
             + 8.0 * d_o * (P - n) + out_bytes * d_o * n - transform_self_bytes(st, d_o, out_bytes, counts=False))
+
+
+def gathered_layer_bytes(st: dict, n: int, e: int, d_in: int, in_bytes: int, d_o: int, out_bytes: int) -> float:
+    """Algorithmic HBM bytes of a sampled layer that is aggregated by
+    destination: every in-list read by the sampler (4 e, and its offsets), the
+    kept lists and their offsets written and read, the input rows read and
+    written once into the table, every message's row and every vertex's own
+    row read from it, every output row written."""
+    kept = st["messages"]
+    row = float(d_in * in_bytes)
+    return 4.0 * e + 8.0 * n + 2 * (4.0 * kept + 8.0 * n) + 2 * n * row + (kept + n) * row + float(n) * d_o * out_bytes
 
 
 def transform_self_bytes(st: dict, d_o: int, out_bytes: int, counts: bool = True) -> float:
@@ -843,12 +859,17 @@ def bench_sage3_100m(args):
     layers = []
     sc_bytes = sc_ms = 0.0
     sc_launches = 0
+    timed_bytes = timed_ms = 0.0
     for li in range(nl):
         sts = [r[li] for r in runs]
         st = sts[-1]
         d_o, d_in = specs[li]["d_out"], specs[li]["d_in"]
         ob = 4 if specs[li]["out_dtype"] == F.F32 else 2
+        ib = 4 if specs[li]["in_dtype"] == F.F32 else 2
         wall = float(np.mean([x["wall_ms"] for x in sts]))
+        lb = gathered_layer_bytes(st, w.n, w.e, d_in, ib, d_o, ob)
+        timed_bytes += lb
+        timed_ms += wall
         prof = [prof_pass[li]] if profile else []  # the pass with events (and the self-message counts)
         kb = sampled_scatter_bytes(prof[0], w.n, d_o, ob, sage=True) if prof else None
         ms_sc = float(np.mean([x["ms_scatter"] for x in prof])) if prof else 0.0
@@ -862,6 +883,7 @@ def bench_sage3_100m(args):
             "vertices_per_s": round(w.n / (wall * 1e-3), 1),
             "init_ms": round(float(np.mean([x["ms_init"] for x in sts])), 3),
             "sample_and_index_ms": round(float(np.mean([x["ms_index"] for x in sts])), 3),
+            "algorithmic_gb": round(lb / 1e9, 3), "gbs": round(lb / (wall * 1e-3) / 1e9, 1),
             "scatter_ms": round(ms_sc, 3), "scatter_algorithmic_gb": round(kb / 1e9, 3) if kb else None,
             "scatter_gbs": round(kb / (ms_sc * 1e-3) / 1e9, 1) if ms_sc > 0 and kb else None,
             "self_in_transform": st["self_in_transform"],
@@ -869,10 +891,15 @@ def bench_sage3_100m(args):
         })
     total_edges = sum(l["edges"] for l in layers)
     value = total_edges / (ms_step * 1e-3) / 1e9
-    roofline = None
+    achieved = timed_bytes / (timed_ms * 1e-3) / 1e9
+    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
+                "kernel": "the timed layers: in-edge lists, sampler, row table, gather",
+                "bytes_per_step": round(timed_bytes, 0)}
+    broadcast = None
     if profile and sc_ms > 0:
         achieved = sc_bytes / (sc_ms * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        broadcast = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": None if args.scale > 1 or args.chunk > 0 else profiled_traffic(w.name),
                     "kernel": "k_scatter",
@@ -936,7 +963,7 @@ def bench_sage3_100m(args):
                 "peak": round(cap, 1), "unit": "TFLOP/s", "frac": round(tf / cap, 4),
                 "mfma_peak": BF16_MFMA_PEAK_TFLOPS, "ai_flop_per_byte": round(ai, 1),
                 "achieved_gbs": round(gb / (gms * 1e-3) / 1e9, 1), "kernel": "k_gemm_panel (bf16)",
-                "note": "untimed pass with events around every kernel"}
+                "note": "untimed pass with events around every kernel, which broadcasts the layers' chunks"}
 
     if need_rows:
         import oracle as O
@@ -981,11 +1008,12 @@ def bench_sage3_100m(args):
                                "hash rank; RMAT(0.57,0.19,0.19) "
                                f"{w.n:,} vertices / {w.e:,} edges; N(0,1) bf16 features, fp32 accumulation; "
                                f"{w.chunk:,}-vertex source chunks; step = CSR build + per layer sampler, chunk "
-                               "index and chunk pushes",
+                               "pushes and aggregation",
                    "n": w.n, "e": w.e, "chunk": w.chunk, "csr_ms": round(csr_ms, 3),
                    "layers_ms": round(layers_ms, 3), **({"scale": f"1/{args.scale}"} if args.scale > 1 else {})},
         "per_layer": layers,
         "roofline": roofline,
+        "broadcast_roofline": broadcast,
         "gemm_roofline": gemm,
         "cpu_baseline": cpu,
         "oracle_check": check,

@@ -92,3 +92,14 @@ def test_self_counts_needed_for_transform_layers():
           "self_in_transform": 3, "self_fresh": -1, "self_last": -1}
     with pytest.raises(ValueError):
         bench.sampled_scatter_bytes(st, 5, 8, 2, sage=True)
+
+
+def test_gathered_layer_bytes():
+    """A sampled layer aggregated by destination, array by array."""
+    n, e, kept, d_in, d_o = 100, 900, 250, 128, 256
+    in_off, in_src = np.zeros(n + 1, np.int64), np.zeros(e, np.int32)
+    off, lst = np.zeros(n, np.int64), np.zeros(kept, np.int32)
+    x, out = np.zeros((n, d_in), np.uint16), np.zeros((n, d_o), np.uint16)
+    want = (in_off[:n].nbytes + in_src.nbytes + 2 * (off.nbytes + lst.nbytes) + 2 * x.nbytes
+            + kept * x[0].nbytes + x.nbytes + out.nbytes)
+    assert bench.gathered_layer_bytes({"messages": kept}, n, e, d_in, 2, d_o, 2) == want
