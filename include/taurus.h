@@ -418,16 +418,18 @@ void taurus_plan_destroy(taurus_plan* plan);
  * every vertex's pending-message count to |M(v)| + 1 (the self message
  * counts as one arrival).  Without a budget the dense accumulators are
  * allocated first and hold the index build's temporaries until the first
- * push.  A sampled in-core layer with device outputs, no profile, fp32 or
- * bf16 inputs of at most 256 columns whose rows take at most 8 * d_out
- * bytes, and a sample that leaves out some edge, is aggregated by
- * destination instead: it keeps the sample as in-edge lists, its pushes copy
- * x into a table of all rows, and the push of the last chunk evaluates every
- * destination (with chunks missing, taurus_finalize evaluates those whose
- * messages have all been pushed).  If its first chunk comes from the host, or
- * the device cannot hold the table, it is broadcast like the others.  Which
- * of the two is known, and their memory taken, at the first push: that push
- * may block, and may return TAURUS_E_OOM (the handle is then poisoned).
+ * push.  A sampled in-core SAGE, GCN or linear GIN layer with device outputs,
+ * no profile, fp32 or bf16 inputs of at most 256 columns whose rows take at
+ * most 8 * d_out bytes, and a sample that leaves out some edge is aggregated
+ * by destination instead, unless its lists are so long for its chunks that
+ * reading input rows would cost more: it keeps the sample as in-edge lists,
+ * its pushes copy x into a table of all rows, and the push of the last chunk
+ * evaluates every destination (with chunks missing, taurus_finalize evaluates
+ * those whose messages have all been pushed).  If its first chunk comes from
+ * the host, the device cannot hold the table, or a weight is not finite in
+ * in_dtype, it is broadcast like the others.  Which of the two is known, and
+ * their memory taken, at the first push: that push may block, and may return
+ * TAURUS_E_OOM (the handle is then poisoned).
  * *out receives the handle.  Blocks until the index is built or the sample
  * drawn.
  * Errors: TAURUS_E_INVALID for bad arguments or a graph that is not a valid

@@ -16,10 +16,11 @@
 // What bounds it: a message costs one read of its source's input row (256 B
 // at 128 bf16 inputs) instead of 1 KiB of transformed row and 2 KiB of
 // accumulator row at 256 outputs.  12.5M destinations, 128 -> 256 bf16,
-// fanout 15: the 4.4M with messages take 3.9 ms (random rows, about 2.8
-// TB/s), the 8.1M without 1.2 ms (5.4 TB/s, the rate of a large copy), the
-// table 1.5 ms (4.3 TB/s).  The broadcast took 18.9 ms of scatter and 8.6 ms
-// of transform.
+// fanout 15: the 5.8M with messages (35.6M of them) take 3.9 ms (13.8 GB
+// counted, 3.5 TB/s of random rows; 390 TFLOP/s of products, the matrix cores
+// busy for 0.70 of the compute units' busy cycles), the 6.7M without 1.2 ms
+// (5.2 GB, 4.4 TB/s; 0.72), the table 1.5 ms (6.4 GB, 4.2 TB/s).  The
+// broadcast took 18.9 ms of scatter and 8.6 ms of transform.
 #include <algorithm>
 #include <vector>
 
@@ -385,7 +386,7 @@ void k_gather_resident(GatherArgs g, int64_t end) {
 // aggregate's products in g.partial for positions before `parts`, the whole
 // value past them (destinations without messages).  A streaming kernel: the
 // rows of the next tile (two where registers allow) are in flight while one
-// is multiplied.  8.1M rows 128 -> 256 bf16: 2.45 ms with the bias loaded from
+// is multiplied.  6.7M rows 128 -> 256 bf16: 2.45 ms with the bias loaded from
 // memory and 8-byte stores of integer-rounded values, 1.16 ms as it is.
 template <int DT, int KB, int NBG, int WAVES>
 __global__ __launch_bounds__(256 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES)))

@@ -2286,18 +2286,19 @@ static void scatter_init(taurus_layer* L, hipStream_t s, const SampleLists* list
     }
 }
 
-// Whether a layer is aggregated by destination once its chunks are there
-// (gather.hip) instead of broadcast chunk by chunk: sampled layers in core, whose kept
-// lists are short, when a message's input row is less to read than the
-// accumulator row it would read and write (both 4 d_out bytes) and the table
-// of input rows takes at most twice the accumulators' memory, which is the
-// same line.  Not with profile (the broadcast's launches are what it times)
-// or host outputs (rows leave as they complete there).  16 floating-point
-// bits means bf16: an fp32 aggregate is three exact bf16 parts, but not
-// three fp16 ones.
+// Whether a layer may be aggregated by destination once its chunks are there
+// (gather.hip) instead of broadcast chunk by chunk (gather_pays decides by its
+// sample): sampled layers in core, when a message's input row is less to read
+// than the accumulator row it would read and write (both 4 d_out bytes).  On
+// the same line the table of input rows takes at most twice the accumulators'
+// memory; where the kernels split, the partial products take as much as the
+// accumulators once more.  Not with profile (the broadcast's launches are what
+// it times) or host outputs (rows leave as they complete there).  16
+// floating-point bits means bf16: an fp32 aggregate is three exact bf16 parts,
+// but not three fp16 ones.
 // Measured, kernel time of a layer past sampling, broadcast -> gather: 12.5M
-// vertices, 200M edges, fanout 15, 128 -> 256 bf16: 27.5 -> 6.5 ms (of which
-// the table 1.5); 3M, 48M, fanout 5, 256 -> 172: 5.0 -> 2.7 ms; 20K, 300K,
+// vertices, 200M edges, fanout 15, 128 -> 256 bf16: 27.5 -> 6.6 ms (of which
+// the table 1.5); 3M, 48M, fanout 5, 256 -> 172: 5.0 -> 2.6 ms; 20K, 300K,
 // fanouts 10 and 5, two layers: 0.15 -> 0.06 ms.
 static bool gather_rule(const taurus_layer_desc& d) {
     const int64_t in_bytes = (int64_t)d.d_in * (d.in_dtype == TAURUS_F32 ? 4 : 2);
