@@ -2312,7 +2312,8 @@ static bool gather_rule(const taurus_layer_desc& d) {
 // input row and, as issue and latency, 512 bytes more, for as many messages as
 // the waves' rounds hold (16 destinations take as many as their longest list;
 // ordered by length they take their own); or, where that is more, the longest
-// list's rows one after the other, 1.7 us for each 256 bytes.  Broadcast: each
+// list's rows one after the other, 1.7 us for each 256 bytes; and, in bf16, the
+// products of an aggregate's two further parts (390 TFLOP/s).  Broadcast: each
 // message's transformed row and 384 bytes of index, each segment's
 // accumulator row in and out, and 2 GB for the index's launches and
 // synchronisations (GCN, whose norms draw the sample again: 1,000 bytes a
@@ -2328,7 +2329,8 @@ static bool gather_pays(const taurus_layer* L) {
     const SampleLists& l = L->lists;
     const int64_t in = (int64_t)d.d_in * (d.in_dtype == TAURUS_F32 ? 4 : 2), out = (int64_t)d.d_out * 4;
     const int64_t held = L->n >= GATHER_ORDER_MIN ? l.kept : 16 * l.rounds;
-    return std::max(held * (in + 512), l.longest * in * 50000) <=
+    const int64_t parts = d.in_dtype == TAURUS_BF16 ? l.nonzero * d.d_in * d.d_out / 13 : 0;
+    return std::max(held * (in + 512), l.longest * in * 50000) + parts <=
            l.kept * (out + 384) + 2 * l.segments * out + 2000000000 +
                (d.agg == TAURUS_GCN_SYM ? l.kept * 1000 + l.longest * 10000000 : 0);
 }
