@@ -429,12 +429,12 @@ def test_weights_that_are_not_finite(torch_cuda, agg, dt):
     x = x.bfloat16() if dt else x
     x[11] = 0
     for bad in (np.inf, np.nan, 3.4e38):
-        W = (rng.standard_normal((64, 32 if agg == SAGE else 16)) / 8).astype(np.float32)
+        W = (rng.standard_normal((64, 64 if agg == SAGE else 32)) / 8).astype(np.float32)
         W[5, 3] = bad
         got = []
         for profile in (1, 0):
-            out = torch.full((n, 16), -7.0, device="cuda")
-            L = T.Layer(n, row_off, col_dst, agg=agg, d_in=64, d_out=16, weight_cat=W, bias=None, out=out,
+            out = torch.full((n, 32), -7.0, device="cuda")
+            L = T.Layer(n, row_off, col_dst, agg=agg, d_in=64, d_out=32, weight_cat=W, bias=None, out=out,
                         in_dtype=dt, fanout=4, layer=1, seed=3, chunk=192, profile=profile)
             L.push_all(x)
             L.finalize()
@@ -457,14 +457,16 @@ def test_sums_past_the_type_before_the_linear_map(torch_cuda, agg, dt, n):
     """Inputs whose sum over a list exceeds fp32 while the outputs do not."""
     torch = torch_cuda
     src, dst, row_off, col_dst = _graph(torch, n, 6 * n, 5)
-    L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, 256, 16, dt, F32, 6, chunk=65536)
+    L, x, W, b, out = _layer(torch, n, row_off, col_dst, agg, 256, 128, dt, F32, 6, chunk=65536)
     xd = x.cuda()
     xd[:, 9] = 1e38
+    _fail_alloc("work lists")                       # the layer is gathered
     L.push_all(xd)
     L.finalize()
+    _fail_alloc(None)
     words, _ = L.sampled_edges()
     L.destroy()
-    z = _reference(agg, n, src, dst, words, xd.double().cpu().numpy(), W, b, True, 16)
+    z = _reference(agg, n, src, dst, words, xd.double().cpu().numpy(), W, b, True, 128)
     assert np.abs(z).max() > 1e36
     _check(out, z, F32)
 
