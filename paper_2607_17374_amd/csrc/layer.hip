@@ -2318,9 +2318,9 @@ static bool gather_rule(const taurus_layer_desc& d) {
 // accumulator row in and out, and 2 GB for the index's launches and
 // synchronisations (GCN, whose norms draw the sample again: 1,000 bytes a
 // message and 10 MB an entry of the longest list more).  Measured over 150
-// samples of 20K to 1M vertices (4 to 400 in-edges, fanouts 1 to 512, rows of 128 to
-// 1,024 bytes in and 64 to 1,024 out), broadcast / gather time: lists of at
-// most 64 mostly 1.05 to 2.5; 200K vertices, 100 in-edges, fanout 256,
+// samples of 20K to 1M vertices (4 to 400 in-edges, fanouts 1 to 512, rows of
+// 128 to 1,024 bytes in and 64 to 1,024 out), broadcast / gather time: lists
+// of at most 64 mostly 1.05 to 2.5; 200K vertices, 100 in-edges, fanout 256,
 // 256 -> 128 fp32 2.87 / 6.41 ms, 128 -> 128 bf16 2.79 / 4.08; 400K, the same,
 // 5.32 / 6.75 and 5.12 / 4.81; 1M vertices, 4 in-edges, hubs of 512 and more,
 // fanout 512, 64 -> 64 fp32 2.22 / 2.80.
